@@ -1,0 +1,60 @@
+"""Kernels at the sizes where their paths change: tile edges, remainders,
+alignment, the ends of a dispatch rule. Each against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2608_27735_amd import synthetic as S
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def api():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2608_27735_amd import api as A
+    return A
+
+
+def dev():
+    return torch.device("cuda:0")
+
+
+def say(*a):
+    print("[case]", *a, flush=True)
+
+
+@pytest.mark.parametrize("offset", [0, 1, 4])
+@pytest.mark.parametrize("count", [1, 3, 4095, 4096, 4097, 8195])
+def test_adam_workgroup_edges(api, count, offset):
+    """Counts around the 4,096 elements of a workgroup, aligned and not, beside
+    a second group; elements before and after the arrays stay as they were.
+    Bars: each moment's rounding on its terms' magnitudes, the update's on its
+    own (fp32 evaluation: a few 2^-24 each)."""
+    r = S.rng(300 + count + offset)
+    say("adam", count, offset)
+    f = np.float32
+    host = [r.normal(size=count + offset + 8).astype(f) for _ in range(4)]
+    host[3] = np.abs(host[3])
+    big = [torch.from_numpy(h).to(dev()) for h in host]
+    view = [b[offset:offset + count] for b in big]
+    other = [torch.ones(5, device=dev()) for _ in range(4)]
+    api.adam_step(dict(a=view[0], b=other[0]), dict(a=view[1], b=other[1]),
+                  dict(a=view[2], b=other[2]), dict(a=view[3], b=other[3]), 1e-2, 7)
+    torch.cuda.synchronize()
+    got = [b.cpu().numpy() for b in big]
+    keep = np.ones(count + offset + 8, bool)
+    keep[offset:offset + count] = False
+    for h, g in zip(host, got):
+        assert np.array_equal(h[keep], g[keep])
+    assert np.array_equal(host[1], got[1])
+    t0, g0, m0, v0 = (h[offset:offset + count].astype(np.float64) for h in host)
+    b1, b2, lr = float(f(0.9)), float(f(0.999)), float(f(1e-2))
+    rt, rm, rv = O.adam(t0, g0, m0, v0, lr, b1, b2, float(f(1e-15)), 7)
+    gt, _, gm, gv = (g[offset:offset + count].astype(np.float64) for g in got)
+    assert np.all(np.abs(gm - rm) <= 3e-7 * (b1 * np.abs(m0) + (1 - b1) * np.abs(g0)))
+    assert np.all(np.abs(gv - rv) <= 3e-7 * (b2 * v0 + (1 - b2) * g0 * g0))
+    step = lr / (1 - b1 ** 7) * (b1 * np.abs(m0) + (1 - b1) * np.abs(g0))
+    denom = np.sqrt(rv / (1 - b2 ** 7)) + float(f(1e-15))
+    assert np.all(np.abs(gt - rt) <= 4e-7 * np.abs(t0) + 2e-6 * step / denom)
