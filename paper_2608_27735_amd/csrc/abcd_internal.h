@@ -80,8 +80,8 @@ __device__ __forceinline__ bool tile_rect(float u, float v, float rx, float ry, 
 }
 
 // A screen-space Gaussian as the blend kernels stage it in LDS: the conic is
-// pre-scaled so that p2 = qa dx^2 + qb dx dy + qc dy^2 = power * log2(e), and
-// alpha = min(alpha_max, o 2^p2) is one v_exp_f32 away.
+// pre-scaled so that (qa dx + qb dy)^2 + (qc dy)^2 = -power * log2(e), and alpha
+// is one v_exp_f32 away.
 constexpr float kLog2e = 1.4426950408889634f;
 
 // conic_opacity holds (l11, l21, l22, o): the conic [[a, b], [b, c]] as its
@@ -89,7 +89,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 struct Splat {
   float u, v;          // mean
   float qa, qb, qc;    // s l11, s l21, s l22 with s^2 = log2(e) / 2
-  float o;             // opacity
+  float lo;            // log2 of the opacity
 };
 
 constexpr float kHalfLog2eSqrt = 0.84932180028801904f;  // sqrt(log2(e) / 2)
@@ -101,7 +101,7 @@ __device__ __forceinline__ Splat make_splat(float2 m, float4 co) {
   s.qa = kHalfLog2eSqrt * co.x;
   s.qb = kHalfLog2eSqrt * co.y;
   s.qc = kHalfLog2eSqrt * co.z;
-  s.o = co.w;
+  s.lo = __builtin_amdgcn_logf(co.w);
   return s;
 }
 
@@ -111,31 +111,26 @@ __device__ __forceinline__ float3 conic_of(float4 co) {
   return make_float3(co.x * co.x, co.x * co.y, co.y * co.y + co.z * co.z);
 }
 
-// Alpha of a splat at pixel offset (dx, dy) = centre - mean. The forward and
-// backward kernels both call this one function, so their skip and clamp
-// decisions are bit-identical.
-struct AlphaEval {
-  float alpha;   // clamped alpha (valid when !skip)
-  float raw;     // o * exp(power), before the clamp
-  float e;       // exp(power)
-  bool skip;     // power > 0 or alpha < alpha_min
-  bool clamped;  // o * exp(power) > alpha_max
-};
-
-__device__ __forceinline__ AlphaEval eval_alpha(float dx, float dy, float qa, float qb, float qc,
-                                                float o, float alpha_min, float alpha_max) {
-  AlphaEval r;
-  // -log2(e) q / 2 with q = d^T L L^T d: minus a sum of two squares
+// Alpha of a splat at pixel offset (dx, dy) = centre - mean, before the clamp
+// to alpha_max: o exp(power), as 2^(log2 o - log2(e) q / 2) with q = d^T L L^T d
+// a sum of two squares, which saves the product with o in every (pixel, entry).
+// The forward and backward kernels call this one function, so their skip and
+// clamp decisions are bit-identical.
+__device__ __forceinline__ float splat_alpha_raw(float dx, float dy, float qa, float qb, float qc,
+                                                 float lo) {
   const float e1 = qa * dx + qb * dy, e2 = qc * dy;
-  const float p2 = -(e1 * e1 + e2 * e2);
-  r.e = __builtin_amdgcn_exp2f(p2);
-  r.raw = o * r.e;
-  r.clamped = r.raw > alpha_max;
-  r.alpha = fminf(r.raw, alpha_max);  // raw is finite: the clamp
-  // alpha_min <= alpha_max (checked on the host), so the clamped alpha is
-  // below alpha_min exactly when the raw value is
-  r.skip = (p2 > 0.0f) || (r.raw < alpha_min);
-  return r;
+  return __builtin_amdgcn_exp2f(fmaf(-e1, e1, fmaf(-e2, e2, lo)));
+}
+__device__ __forceinline__ float splat_alpha(float dx, float dy, float qa, float qb, float qc,
+                                             float lo, float alpha_max) {
+  return fminf(splat_alpha_raw(dx, dy, qa, qb, qc, lo), alpha_max);
+}
+
+// bits = 2 bits + bit, one instruction (every lane of the wave active).
+__device__ __forceinline__ uint32_t shift_in(uint32_t bits, bool bit) {
+  const uint64_t m = __ballot(bit);
+  asm("v_addc_co_u32_e64 %0, vcc, %0, %0, %1" : "+v"(bits) : "s"(m) : "vcc");
+  return bits;
 }
 
 // Wave64 sum with DPP row operations; the total is returned to every lane.

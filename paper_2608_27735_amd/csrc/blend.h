@@ -73,24 +73,6 @@ __device__ __forceinline__ TileBox tile_box(const BlendConsts& k, int tile) {
   return b;
 }
 
-// Block-wide stream compaction of this thread's entry into slot `*pos`;
-// returns the number kept. s_wcnt holds 4 wave counts.
-__device__ __forceinline__ int compact(bool keep, int* s_wcnt, int& pos) {
-  const int w = threadIdx.x >> 6;
-  const uint64_t bal = __ballot(keep);
-  if ((threadIdx.x & 63) == 0) s_wcnt[w] = __popcll(bal);
-  __syncthreads();
-  int off = 0, tot = 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int c = s_wcnt[k];
-    off += k < w ? c : 0;
-    tot += c;
-  }
-  pos = off + __popcll(bal & ((1ull << (threadIdx.x & 63)) - 1ull));
-  return __builtin_amdgcn_readfirstlane(tot);  // uniform: loops over it branch on scalars
-}
-
 // Tile test and rows mask of an entry in one: bit w set when some pixel
 // centre of rows 4w .. 4w + 3 of the tile (clipped to the image) can see the
 // Gaussian with alpha >= alpha_min, i.e. d^T Q d <= tau = 2 ln(o / alpha_min);
@@ -145,7 +127,7 @@ __device__ __forceinline__ uint32_t splat_rows_single(float u, float v, float a,
   return rows;
 }
 
-// Block-wide compaction of the staged entries (as compact() does) and, for
+// Block-wide compaction of the staged entries into slots `pos` and, for
 // each wave w, the list of the staged slots whose rows mask has bit w, in
 // list order, into s_idx[w]. s_cnt holds 5 x 4 wave counts. Returns the
 // number kept; wcnt is the length of the calling wave's list (both uniform).
@@ -185,6 +167,41 @@ __device__ __forceinline__ int compact_rows(bool keep, uint32_t rows, int (*s_cn
   return __builtin_amdgcn_readfirstlane(tot);
 }
 
+// The same for kernels whose waves each walk a contiguous copy of their own
+// list: at[r] is this thread's slot in the list of band r (valid where bit r
+// of rows is set), wcnt the length of the calling wave's list; returns the
+// number of entries with any bit set (wcnt and the result are uniform). s_cnt
+// holds 5 x 4 wave counts.
+__device__ __forceinline__ int band_slots(uint32_t rows, int (*s_cnt)[4], int (&at)[4], int& wcnt) {
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const uint64_t below = (1ull << l) - 1ull;
+  const uint64_t bal = __ballot(rows != 0u);
+  uint64_t rb[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) rb[r] = __ballot((rows >> r) & 1u);
+  if (l == 0) {
+    s_cnt[0][w] = __popcll(bal);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s_cnt[1 + r][w] = __popcll(rb[r]);
+  }
+  __syncthreads();
+  int tot = 0, mine = 0;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    tot += s_cnt[0][v];
+    mine += s_cnt[1 + w][v];
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    int o = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) o += v < w ? s_cnt[1 + r][v] : 0;
+    at[r] = o + __popcll(rb[r] & below);
+  }
+  wcnt = __builtin_amdgcn_readfirstlane(mine);
+  return __builtin_amdgcn_readfirstlane(tot);
+}
+
 // Frames of at most this many tiles (without a split) take the forward and
 // backward kernels that give each tile four workgroups, one pixel row per
 // wave and four list entries per step of a wave.
@@ -208,7 +225,7 @@ __device__ __forceinline__ Swapped swap_bit5(float x) {
   return Swapped{__int_as_float(p[0]), __int_as_float(p[1])};
 }
 
-constexpr int kGroup = 8;
+constexpr int kGroup = 4;  // the forward's group (six spilled four registers)
 constexpr int kBwdGroup = 4;  // the backward's group (register budget: 5 waves per SIMD)
 
 BlendConsts consts(const abcd_camera& cam, const abcd_raster_params& prm) {

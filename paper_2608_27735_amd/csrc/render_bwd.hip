@@ -86,7 +86,7 @@ __device__ __forceinline__ void bwd_item(
     const uint32_t* __restrict__ last, const float4* __restrict__ dL_dout, float* __restrict__ g2d,
     int64_t gs, const SplitLayout& sp) {
   __shared__ float4 s_ga[256];  // u, v, qa, qb
-  __shared__ float4 s_gb[256];  // qc, o, r, g
+  __shared__ float4 s_gb[256];  // qc, log2 o, r, g
   __shared__ float4 s_gc[256];  // a, b, c (conic), colour b
   __shared__ int s_pos[256];
   __shared__ uint32_t s_g[256];
@@ -192,7 +192,7 @@ __device__ __forceinline__ void bwd_item(
     if (keep) {
       const Splat sp = make_splat(rec.m, rec.co);
       s_ga[pos] = make_float4(sp.u, sp.v, sp.qa, sp.qb);
-      s_gb[pos] = make_float4(sp.qc, sp.o, rec.r, rec.g);
+      s_gb[pos] = make_float4(sp.qc, sp.lo, rec.r, rec.g);
       s_gc[pos] = make_float4(cn.x, cn.y, cn.z, rec.b);
       s_pos[pos] = (int)(bend - 1 - tid - start);
       s_g[pos] = rec.gid;
@@ -241,13 +241,13 @@ __device__ __forceinline__ void bwd_item(
       const float4 ga = gav[i], gb = gbv[i];
       if (kk >= wml) continue;  // wave-uniform: no pixel of this wave reaches entry kk
       const float dx = fx - ga.x, dy = fy - ga.y;
-      const AlphaEval ae = eval_alpha(dx, dy, ga.z, ga.w, gb.x, gb.y, k.alpha_min, k.alpha_max);
-      const bool contrib = kk < lastp && !ae.skip;
+      const float raw = splat_alpha_raw(dx, dy, ga.z, ga.w, gb.x, gb.y);
+      const bool contrib = kk < lastp && raw >= k.alpha_min;
       if (!__ballot(contrib)) continue;  // wave-uniform
       // Branch-free per lane: a lane that does not blend this entry takes
       // alpha = 0, which leaves T and R unchanged, and a zero mask on the
       // alpha-derivative terms.
-      const float a = contrib ? (ae.clamped ? k.alpha_max : ae.raw) : 0.0f;
+      const float a = contrib ? fminf(raw, k.alpha_max) : 0.0f;
       const float om = 1.0f - a;
       const float iom = __builtin_amdgcn_rcpf(om);  // om >= 1 - alpha_max > 0
       const float Tk = T * iom;
@@ -260,7 +260,7 @@ __device__ __forceinline__ void bwd_item(
       const float dLda = Tk * (CG - RG) - iom * TgT;
       RG = a * CG + om * RG;
       T = Tk;
-      const float dm = (contrib && !ae.clamped) ? dLda : 0.0f;
+      const float dm = (contrib && raw <= k.alpha_max) ? dLda : 0.0f;
       const float gp = a * dm;
       // first and second moments of gp over the pixels; the conic and the
       // constant factors are applied once per entry at the flush
@@ -270,7 +270,7 @@ __device__ __forceinline__ void bwd_item(
       gr[2] = q * dx;
       gr[3] = q * dy;
       gr[4] = r * dy;
-      gr[5] = ae.e * dm;
+      gr[5] = gp;
       const Sum9 v = wave_sum9(gr, lane);
       float out = lane == 48 ? v.v8 : v.lo;
       asm volatile("" : "+v"(out));  // the last folds stay outside the branch (DPP add)
@@ -292,6 +292,7 @@ __device__ __forceinline__ void bwd_item(
       g[2] = -0.5f * g[2];
       g[3] = -g[3];
       g[4] = -0.5f * g[4];
+      g[5] *= __builtin_amdgcn_exp2f(-s_gb[tid].y);  // gp = o d alpha / d o: over the opacity
       float* dst = g2d + s_g[tid];
 #pragma unroll
       for (int q = 0; q < 9; ++q)
@@ -401,7 +402,7 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
     const float* __restrict__ final_T, const uint32_t* __restrict__ last,
     const float4* __restrict__ dL_dout, float* __restrict__ g2d, int64_t gs) {
   __shared__ float4 s_ga[256];  // u, v, qa, qb
-  __shared__ float4 s_gb[256];  // qc, o, r, g
+  __shared__ float4 s_gb[256];  // qc, log2 o, r, g
   __shared__ float4 s_gc[256];  // a, b, c (conic), colour b
   __shared__ int s_pos[256];
   __shared__ uint32_t s_g[256];
@@ -470,7 +471,7 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
     if (keep) {
       const Splat sp = make_splat(rec.m, rec.co);
       s_ga[pos] = make_float4(sp.u, sp.v, sp.qa, sp.qb);
-      s_gb[pos] = make_float4(sp.qc, sp.o, rec.r, rec.g);
+      s_gb[pos] = make_float4(sp.qc, sp.lo, rec.r, rec.g);
       s_gc[pos] = make_float4(cn.x, cn.y, cn.z, rec.b);
       s_pos[pos] = (int)(bend - 1 - tid - start);
       s_g[pos] = rec.gid;
@@ -495,10 +496,10 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
       const uint32_t kk = (uint32_t)s_pos[j];
       if (!__ballot(valid && kk < wml)) continue;  // wave-uniform
       const float dx = fx - ga.x, dy = fy - ga.y;
-      const AlphaEval ae = eval_alpha(dx, dy, ga.z, ga.w, gb.x, gb.y, k.alpha_min, k.alpha_max);
-      const bool contrib = valid && kk < lastp && !ae.skip;
+      const float raw = splat_alpha_raw(dx, dy, ga.z, ga.w, gb.x, gb.y);
+      const bool contrib = valid && kk < lastp && raw >= k.alpha_min;
       if (!__ballot(contrib)) continue;  // wave-uniform
-      const float a = contrib ? (ae.clamped ? k.alpha_max : ae.raw) : 0.0f;
+      const float a = contrib ? fminf(raw, k.alpha_max) : 0.0f;
       const float iom = __builtin_amdgcn_rcpf(1.0f - a);  // 1 - a >= 1 - alpha_max > 0
       // transmittance before each entry: T times the inclusive prefix product
       // of 1 / (1 - alpha) over the step's entries, back to front
@@ -521,7 +522,7 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
       const float dLda = Tk * CG - iom * (behind + TgT);
       T *= ptot;
       S += stot;
-      const float dm = (contrib && !ae.clamped) ? dLda : 0.0f;
+      const float dm = (contrib && raw <= k.alpha_max) ? dLda : 0.0f;
       const float gp = a * dm;
       const float q = gp * dx, r = gp * dy;
       float gr[9];
@@ -530,7 +531,7 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
       gr[2] = q * dx;
       gr[3] = q * dy;
       gr[4] = r * dy;
-      gr[5] = ae.e * dm;
+      gr[5] = gp;
       gr[6] = wgt * gcr;
       gr[7] = wgt * gcg;
       gr[8] = wgt * gcb;
@@ -552,6 +553,7 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
       g[2] = -0.5f * g[2];
       g[3] = -g[3];
       g[4] = -0.5f * g[4];
+      g[5] *= __builtin_amdgcn_exp2f(-s_gb[tid].y);  // gp = o d alpha / d o: over the opacity
       float* dst = g2d + s_g[tid];
 #pragma unroll
       for (int q = 0; q < 9; ++q)

@@ -29,11 +29,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
     float4* __restrict__ out, float* __restrict__ final_T, uint32_t* __restrict__ last,
     unsigned long long* __restrict__ n_blends, const uint32_t* __restrict__ order,
     uint2* __restrict__ out16, int* __restrict__ rect, int fb_stop, SplitLayout sp) {
-  __shared__ float4 s_ga[256];  // u, v, qa, qb
-  __shared__ float4 s_gb[256];  // qc, o, r, g
-  __shared__ float4 s_bl[256];  // b (16-byte stride: one address serves all three reads)
-  __shared__ int s_pos[256];    // position in the tile's list
-  __shared__ __align__(8) uint8_t s_idx[4][256];  // per wave: staged slots reaching its rows
+  // per wave: the staged entries that reach its rows, in list order, then up
+  // to kGroup - 1 entries that blend nothing; reads run one group ahead
+  constexpr int kSlots = 256 + 2 * kGroup;
+  __shared__ float4 s_ga[4][kSlots];  // u, v, qa, qb
+  __shared__ float2 s_gq[4][kSlots];  // qc, log2 o
+  __shared__ float2 s_rg[4][kSlots];  // r, g
+  __shared__ float s_bl[4][kSlots];   // b
+  __shared__ uint8_t s_at[4][256];    // position in the batch
   __shared__ int s_wcnt[5][4];
   __shared__ unsigned long long s_nb;
   __shared__ uint32_t s_base;
@@ -49,19 +52,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
   const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
   float T = 1.0f, cr = 0.0f, cg = 0.0f, cb = 0.0f;
   uint32_t lastk = 0, nb = 0;
-  bool done = !inside;
+  bool done = !inside;  // before the walk
   // Stop threshold on the next transmittance. The compositing-aware rule
   // (1 - F_a) T_next < t_min is applied as T_next < t_min / (1 - F_a); a pixel
   // whose F leaves it less than t_min of weight blends nothing.
   float thr = k.t_min;
   if (!kHalf && fb_stop && F && inside) {
     const float vis = 1.0f - F[(int64_t)py * k.width + px].w;
-    thr = vis > 0.0f ? k.t_min / vis : __builtin_huge_valf();
-    done = vis < k.t_min;
+    done = vis < k.t_min || !(vis > 0.0f);
+    thr = done ? 0.0f : k.t_min / vis;
   }
-  // alpha below which the lane blends nothing: alpha_min, infinite once the
-  // pixel has stopped
-  float amin_l = done ? __builtin_huge_valf() : k.alpha_min;
+  // alpha below which the lane blends nothing: alpha_min (at least the
+  // smallest positive number: an alpha of zero blends nothing), infinite once
+  // the pixel has stopped
+  float amin_l = done ? __builtin_huge_valf() : fmaxf(k.alpha_min, __FLT_DENORM_MIN__);
   if (tid == 0) {
     s_nb = 0;
     s_walk = 0;
@@ -89,7 +93,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
     rec = gather_rec(gid0, start + tid < end, means2d, conic_opacity, rgb);
   }
   for (uint32_t b0 = start; b0 < end; b0 += 256) {
-    if (__syncthreads_count(done) == 256) break;
+    if (__syncthreads_count(amin_l == __builtin_huge_valf()) == 256) break;
     if (split_ok && b0 > start && (b0 - start) % chd == 0 && (b0 - start) / chd < kMaxChunks) {
       // state after the positions before b0; no pixel walks past a boundary
       // the loop did not reach
@@ -114,16 +118,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
     // pixel rows: the others contribute nothing to any of its pixels
     const uint32_t rows =
         rec.valid ? splat_rows(rec.m.x, rec.m.y, cn.x, cn.y, cn.z, rec.co.w, k.alpha_min, box) : 0u;
-    const bool keep = rows != 0u;
-    int pos, wcnt;
-    const int cnt = compact_rows(keep, rows, s_wcnt, s_idx, pos, wcnt);
-    staged += (uint32_t)cnt;
-    if (keep) {
+    int at[4], wcnt;
+    staged += (uint32_t)band_slots(rows, s_wcnt, at, wcnt);
+    if (rows != 0u) {
       const Splat sp = make_splat(rec.m, rec.co);
-      s_ga[pos] = make_float4(sp.u, sp.v, sp.qa, sp.qb);
-      s_gb[pos] = make_float4(sp.qc, sp.o, rec.r, rec.g);
-      s_bl[pos].x = rec.b;
-      s_pos[pos] = (int)(b0 - start) + tid;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if ((rows >> r) & 1u) {
+          s_ga[r][at[r]] = make_float4(sp.u, sp.v, sp.qa, sp.qb);
+          s_gq[r][at[r]] = make_float2(sp.qc, sp.lo);
+          s_rg[r][at[r]] = make_float2(rec.r, rec.g);
+          s_bl[r][at[r]] = rec.b;
+          s_at[r][at[r]] = (uint8_t)tid;
+        }
+      }
+    }
+    const int w = tid >> 6;
+    if ((tid & 63) < kGroup) {  // the last group's rest: alpha 2^-1e30 = 0
+      const int p = wcnt + (tid & 63);
+      s_ga[w][p] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      s_gq[w][p] = make_float2(0.0f, -1e30f);
+      s_rg[w][p] = make_float2(0.0f, 0.0f);
+      s_bl[w][p] = 0.0f;
     }
     __syncthreads();
     // gathers of the next batch and list values of the one after overlap the
@@ -132,81 +148,94 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
     const uint32_t gid_after = values[min(b0 + 512 + tid, lastpos)];
     rec = gather_rec(gid_next, nxt < end, means2d, conic_opacity, rgb);
     gid_next = gid_after;
-    if (__ballot(!done)) {
-      // The wave walks its own list of staged slots, kGroup entries at a
-      // time; all LDS reads of a group are issued before the first is used,
-      // so the LDS latency is paid once per group.
-      static_assert(kGroup % 4 == 0, "slot indices are read four at a time");
-      const uint32_t* my_idx = reinterpret_cast<const uint32_t*>(s_idx[tid >> 6]);
+    if (__ballot(amin_l < __builtin_huge_valf())) {
+      // The wave walks its own list kGroup entries at a time, 21 vector
+      // instructions per entry: a tile whose walk sets the launch's length has
+      // each SIMD of its CU to a single wave, which issues one instruction
+      // every 4.7 clocks (137 clocks per entry here), so the count is what it
+      // costs. The next group's geometry is read while this one blends and a
+      // group's colours while its alphas are computed, so no LDS latency is
+      // waited for, and consecutive records make two entries one 16-byte read.
+      // Against selects on the stop in every entry and reads through a list of
+      // slots (28 instructions): 1M Gaussians at 1297x840 180 -> 157 us, 300K
+      // 167 -> 144, 4M tiny ones at 2560x1440 486 -> 410.
       int jl = -1;  // position in the wave's list of the last entry the lane blended
-      // One group; kTail: the list ends inside it, and positions past the end
-      // read the group's first entry and blend nothing (every value read is
-      // finite). Returns true when no pixel of the wave is left.
-      auto group = [&](const int j0, auto tail) -> bool {
-        constexpr bool kTail = decltype(tail)::value;
-        uint32_t iw[kGroup / 4];
+      float4 ga[kGroup];
+      float2 gq[kGroup];
 #pragma unroll
-        for (int h = 0; h < kGroup / 4; ++h) iw[h] = __builtin_amdgcn_readfirstlane(my_idx[j0 / 4 + h]);
-        float4 ga[kGroup], gb[kGroup];
+      for (int i = 0; i < kGroup; ++i) {
+        ga[i] = s_ga[w][i];
+        gq[i] = s_gq[w][i];
+      }
+      for (int j0 = 0; j0 < wcnt; j0 += kGroup) {
+        float2 rg[kGroup];
         float bl[kGroup];
 #pragma unroll
         for (int i = 0; i < kGroup; ++i) {
-          int j = (int)((iw[i >> 2] >> (8 * (i & 3))) & 255u);
-          if (kTail && j0 + i >= wcnt) j = (int)(iw[0] & 255u);
-          ga[i] = s_ga[j];
-          gb[i] = s_gb[j];
-          bl[i] = s_bl[j].x;
+          rg[i] = s_rg[w][j0 + i];
+          bl[i] = s_bl[w][j0 + i];
         }
-        // keep the group's reads ahead of the arithmetic (the compiler would
-        // otherwise sink each read to its use)
-#pragma unroll
-        for (int i = 0; i < kGroup; ++i)
-          asm volatile("" ::"v"(ga[i].x), "v"(ga[i].y), "v"(ga[i].z), "v"(ga[i].w), "v"(gb[i].x),
-                       "v"(gb[i].y), "v"(gb[i].z), "v"(gb[i].w), "v"(bl[i]));
         // alpha of each entry at this pixel, 0 where the lane does not blend
-        // it: below alpha_min (eval_alpha's skip: its power is minus a sum of
-        // squares, never positive), or the pixel has stopped (amin_l = inf)
+        // it: below alpha_min, or the pixel has stopped (amin_l = inf)
         float a[kGroup];
+        uint32_t hits = 0;  // entry i of the group in bit kGroup - 1 - i
 #pragma unroll
         for (int i = 0; i < kGroup; ++i) {
-          const AlphaEval ae = eval_alpha(fx - ga[i].x, fy - ga[i].y, ga[i].z, ga[i].w, gb[i].x,
-                                          gb[i].y, k.alpha_min, k.alpha_max);
-          a[i] = ae.alpha < amin_l ? 0.0f : ae.alpha;
-          if (kTail && j0 + i >= wcnt) a[i] = 0.0f;
+          const float al = splat_alpha(fx - ga[i].x, fy - ga[i].y, ga[i].z, ga[i].w, gq[i].x,
+                                       gq[i].y, k.alpha_max);
+          const bool hit = al >= amin_l;
+          a[i] = hit ? al : 0.0f;
+          hits = shift_in(hits, hit);
+        }
+#pragma unroll
+        for (int i = 0; i < kGroup; ++i) {
+          ga[i] = s_ga[w][j0 + kGroup + i];
+          gq[i] = s_gq[w][j0 + kGroup + i];
         }
         // The chain Tc of every hit blended, T (1 - alpha) with one rounding
         // (exactly T where alpha = 0), holds the values of the entry-by-entry
         // walk up to its first stop. T never increases and only hits change
         // it, so an entry blends exactly when its next value is still at or
-        // above the threshold (ok): the first hit below stops the pixel and
-        // every later value is below too. No branch depends on the stop.
-        float Tc = T;
-        int jg = -1;  // the lane's last blended entry of the group
+        // above the threshold: the first hit below stops the pixel and every
+        // later value is below too.
+        float Tc[kGroup + 1], wt[kGroup];
+        Tc[0] = T;
 #pragma unroll
         for (int i = 0; i < kGroup; ++i) {
-          const float Tn = fmaf(-Tc, a[i], Tc);
-          const bool ok = Tn >= thr;
-          // a zero weight adds exactly zero (colours are finite and >= 0)
-          const float wgt = ok ? a[i] * Tc : 0.0f;
-          cr = fmaf(gb[i].z, wgt, cr);
-          cg = fmaf(gb[i].w, wgt, cg);
-          cb = fmaf(bl[i], wgt, cb);
-          const bool blend = ok && a[i] != 0.0f;
-          jg = blend ? i : jg;
-          nb += blend ? 1u : 0u;
-          T = ok ? Tn : T;
-          Tc = Tn;
+          Tc[i + 1] = fmaf(-Tc[i], a[i], Tc[i]);
+          wt[i] = a[i] * Tc[i];
         }
-        jl = jg >= 0 ? j0 + jg : jl;
-        done = done || Tc < thr;
-        amin_l = done ? __builtin_huge_valf() : amin_l;
-        return !__ballot(!done);
-      };
-      int j0 = 0;
-      bool over = false;
-      for (; j0 + kGroup <= wcnt && !over; j0 += kGroup) over = group(j0, std::false_type{});
-      if (!over && j0 < wcnt) group(j0, std::true_type{});
-      if (jl >= 0) lastk = (uint32_t)s_pos[s_idx[tid >> 6][jl]] + 1;
+        const bool stops = Tc[kGroup] < thr;  // not of a lane that had stopped: its a = 0
+        bool none_left = false;
+        if (__ballot(stops)) {
+          // some pixel stops in this group: its entries from the stop on get
+          // weight zero, which adds exactly zero (colours are finite and >= 0)
+          uint32_t kept = 0;
+          float Tk = T;
+#pragma unroll
+          for (int i = 0; i < kGroup; ++i) {
+            const bool ok = Tc[i + 1] >= thr;
+            wt[i] = ok ? wt[i] : 0.0f;
+            kept = shift_in(kept, ok);
+            Tk = ok ? Tc[i + 1] : Tk;
+          }
+          Tc[kGroup] = Tk;
+          hits &= kept;
+          amin_l = stops ? __builtin_huge_valf() : amin_l;
+          none_left = !__ballot(amin_l < __builtin_huge_valf());
+        }
+#pragma unroll
+        for (int i = 0; i < kGroup; ++i) {
+          cr = fmaf(rg[i].x, wt[i], cr);
+          cg = fmaf(rg[i].y, wt[i], cg);
+          cb = fmaf(bl[i], wt[i], cb);
+        }
+        T = Tc[kGroup];
+        nb += (uint32_t)__popc(hits);
+        jl = hits ? j0 + kGroup - __ffs((int)hits) : jl;
+        if (none_left) break;  // wave-uniform
+      }
+      if (jl >= 0) lastk = (b0 - start) + (uint32_t)s_at[w][jl] + 1u;
     }
     // s_wcnt is rewritten only after the next barrier
   }
@@ -288,7 +317,7 @@ __global__ __launch_bounds__(256) void render_fwd_rows_kernel(
     unsigned long long* __restrict__ n_blends, uint2* __restrict__ out16, int* __restrict__ rect,
     int fb_stop) {
   __shared__ float4 s_ga[256];  // u, v, qa, qb
-  __shared__ float4 s_gb[256];  // qc, o, r, g
+  __shared__ float4 s_gb[256];  // qc, log2 o, r, g
   __shared__ float s_bl[256];   // b
   __shared__ int s_pos[256];    // position in the tile's list
   __shared__ __align__(4) uint8_t s_idx[4][256];  // per wave: staged slots reaching its row
@@ -336,7 +365,7 @@ __global__ __launch_bounds__(256) void render_fwd_rows_kernel(
     if (keep) {
       const Splat sp = make_splat(rec.m, rec.co);
       s_ga[pos] = make_float4(sp.u, sp.v, sp.qa, sp.qb);
-      s_gb[pos] = make_float4(sp.qc, sp.o, rec.r, rec.g);
+      s_gb[pos] = make_float4(sp.qc, sp.lo, rec.r, rec.g);
       s_bl[pos] = rec.b;
       s_pos[pos] = (int)(b0 - start) + tid;
     }
@@ -355,11 +384,10 @@ __global__ __launch_bounds__(256) void render_fwd_rows_kernel(
         const int j = my_idx[jw < wcnt ? jw : j0];
         const float4 ga = s_ga[j], gb = s_gb[j];
         const float bl = s_bl[j];
-        const AlphaEval ae = eval_alpha(fx - ga.x, fy - ga.y, ga.z, ga.w, gb.x, gb.y, k.alpha_min,
-                                        k.alpha_max);
-        // 0 where the lane blends nothing: past the list, below alpha_min
-        // (eval_alpha's power is never positive), or the pixel has stopped
-        const float a = (jw < wcnt && !(ae.alpha < amin_l)) ? ae.alpha : 0.0f;
+        const float al = splat_alpha(fx - ga.x, fy - ga.y, ga.z, ga.w, gb.x, gb.y, k.alpha_max);
+        // 0 where the lane blends nothing: past the list, below alpha_min, or
+        // the pixel has stopped
+        const float a = (jw < wcnt && al >= amin_l) ? al : 0.0f;
         const float om = 1.0f - a;
         const Swapped p1 = swap_bit4(om);
         const float t1 = p1.first * p1.second;

@@ -58,3 +58,43 @@ def test_adam_workgroup_edges(api, count, offset):
     step = lr / (1 - b1 ** 7) * (b1 * np.abs(m0) + (1 - b1) * np.abs(g0))
     denom = np.sqrt(rv / (1 - b2 ** 7)) + float(f(1e-15))
     assert np.all(np.abs(gt - rt) <= 4e-7 * np.abs(t0) + 2e-6 * step / denom)
+
+
+@pytest.mark.parametrize("logit", [-4.0, 0.0, 4.0])
+@pytest.mark.parametrize("count", [1, 3, 4, 5, 64, 255, 256, 257, 513])
+def test_forward_list_lengths(api, count, logit):
+    """Lists of 1 to 513 entries in the same few tiles (groups of four, batches
+    of 256 and their remainders), faint, saturating within a group, and opaque,
+    on a frame of 272 tiles (the general kernel); also t_min = 0 (no stop) and
+    an alpha_min that no fp32 alpha falls below. Bars: the parity bars of the
+    forward (max abs 1e-5 off knife-edge pixels) and of the gradients (1e-4)."""
+    from paper_2608_27735_amd.camera import RasterParams, look_at
+    r = S.rng(400 + count)
+    cam = look_at((0.0, -3.0, 0.0), (0, 0, 0), 272, 256)
+    sc = S.gaussians(r, r.uniform(-0.1, 0.1, (count, 3)), 0, np.log(0.1), 0.3)
+    sc["opacity_logits"] = np.full(count, logit, np.float32)
+    F, B = S.background_pair(r, cam.height, cam.width)
+    dL = S.upstream_grad(r, cam.height, cam.width)
+    for kw in (dict(), dict(t_min=0.0), dict(alpha_min=1e-30)):
+        prm = RasterParams(sh_degree=0, **kw)
+        say("list lengths", count, logit, kw)
+        ref = O.step(cam, prm, sc, F=F, B=B, dL_dout=None, rel_margin=1e-4)
+        knife = ref["fwd"]["knife"]
+        up = np.where(knife[..., None], 0, dL).astype(np.float32)
+        ref = O.step(cam, prm, sc, F=F, B=B, dL_dout=up.astype(np.float64), rel_margin=1e-4)
+        d = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to(dev())
+        params = {k: d(v) for k, v in sc.items()}
+        proj = api.project(cam, prm, **params)
+        bins = api.bin_sort(cam.width, cam.height, proj)
+        fwd = api.render_fwd(cam, prm, bins, proj, F=d(F), B=d(B))
+        grads = api.render_bwd(cam, prm, params, proj, bins, fwd, d(up), F=d(F), B=d(B))
+        torch.cuda.synchronize()
+        err = np.abs(fwd["out"].cpu().numpy() - ref["fwd"]["out"])[~knife]
+        assert err.max() <= 1e-5
+        assert np.array_equal(fwd["last"].cpu().numpy().view(np.uint32)[~knife],
+                              ref["fwd"]["last"][~knife])
+        if prm.t_min == 0.0:
+            continue  # 0.5^255 underflows fp32: no backward can recover the walk from final_T
+        for k in params:
+            g, gr = grads[k].cpu().numpy().astype(np.float64), ref["grads"][k]
+            assert np.linalg.norm(g - gr) <= 1e-4 * max(np.linalg.norm(gr), 1e-30), k
