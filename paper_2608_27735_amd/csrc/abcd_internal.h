@@ -93,6 +93,7 @@ struct Splat {
 };
 
 constexpr float kHalfLog2eSqrt = 0.84932180028801904f;  // sqrt(log2(e) / 2)
+constexpr float kHalfLog2e = 0.72134752044448170f;
 
 __device__ __forceinline__ Splat make_splat(float2 m, float4 co) {
   Splat s;
@@ -121,15 +122,30 @@ __device__ __forceinline__ float splat_alpha_raw(float dx, float dy, float qa, f
   const float e1 = qa * dx + qb * dy, e2 = qc * dy;
   return __builtin_amdgcn_exp2f(fmaf(-e1, e1, fmaf(-e2, e2, lo)));
 }
+// min(raw, alpha_max) of a raw alpha >= 0 (one instruction: a plain minimum
+// would first quiet its operands).
+__device__ __forceinline__ float clamp_alpha(float raw, float alpha_max) {
+  return __builtin_amdgcn_fmed3f(raw, 0.0f, alpha_max);
+}
 __device__ __forceinline__ float splat_alpha(float dx, float dy, float qa, float qb, float qc,
                                              float lo, float alpha_max) {
-  return fminf(splat_alpha_raw(dx, dy, qa, qb, qc, lo), alpha_max);
+  return clamp_alpha(splat_alpha_raw(dx, dy, qa, qb, qc, lo), alpha_max);
 }
 
-// bits = 2 bits + bit, one instruction (every lane of the wave active).
-__device__ __forceinline__ uint32_t shift_in(uint32_t bits, bool bit) {
-  const uint64_t m = __ballot(bit);
-  asm("v_addc_co_u32_e64 %0, vcc, %0, %0, %1" : "+v"(bits) : "s"(m) : "vcc");
+// The four flags as bits 3 (the first) to 0, an add with carry each (every lane
+// of the wave active). A vector instruction may read a mask that another one
+// wrote two wait states later at the earliest.
+__device__ __forceinline__ uint32_t bits_of(const bool (&f)[4]) {
+  const uint64_t m0 = __ballot(f[0]), m1 = __ballot(f[1]), m2 = __ballot(f[2]), m3 = __ballot(f[3]);
+  uint32_t bits;
+  asm("s_nop 1\n\t"
+      "v_cndmask_b32_e64 %0, 0, 1, %1\n\t"
+      "v_addc_co_u32_e64 %0, vcc, %0, %0, %2\n\t"
+      "v_addc_co_u32_e64 %0, vcc, %0, %0, %3\n\t"
+      "v_addc_co_u32_e64 %0, vcc, %0, %0, %4"
+      : "=&v"(bits)
+      : "s"(m0), "s"(m1), "s"(m2), "s"(m3)
+      : "vcc");
   return bits;
 }
 

@@ -73,38 +73,53 @@ __device__ __forceinline__ TileBox tile_box(const BlendConsts& k, int tile) {
   return b;
 }
 
-// Tile test and rows mask of an entry in one: bit w set when some pixel
-// centre of rows 4w .. 4w + 3 of the tile (clipped to the image) can see the
-// Gaussian with alpha >= alpha_min, i.e. d^T Q d <= tau = 2 ln(o / alpha_min);
-// 0: the entry is dropped. With the tile's column range fixed, the minimum of
-// the convex quadratic over dx is a convex function of dy whose minimiser y*
-// is 0 when the mean's column lies in the range, else -b dx_e / c on the
-// nearer edge dx_e; the minimum over a band is at y* clamped to the band, with
-// dx = -b dy / a clamped to the columns. The margin keeps every entry whose
-// per-pixel decision could go either way in fp32 (no pixel that blends is
-// ever dropped, so the outputs do not depend on this test).
-__device__ __forceinline__ uint32_t splat_rows(float u, float v, float a, float b, float c, float o,
-                                               float alpha_min, const TileBox& box) {
+// The general kernels give each wave an 8x8 quadrant of the tile (wave w the
+// columns 8 (w & 1) .., rows 8 (w >> 1) ..), lane l pixel (l & 7, l >> 3) of it: a
+// splat of radius r meets a square of 64 pixels less often than a strip of
+// 16x4 ((8 + 2r)^2 against (16 + 2r)(4 + 2r)). Forward, 16x4 strips -> quadrants:
+// 1M Gaussians at 1297x840 151 -> 141 us, 300K 138 -> 129, 4M tiny ones at
+// 2560x1440 390 -> 287 (the strips of its longest walks split worse than its
+// average), the 64K ring scene at 512x512 87 -> 77.
+__device__ __forceinline__ int quad_x(int tid) { return 8 * ((tid >> 6) & 1) + (tid & 7); }
+__device__ __forceinline__ int quad_y(int tid) { return 8 * (tid >> 7) + ((tid >> 3) & 7); }
+
+// Tile test and quadrants mask of an entry in one: bit w set when some pixel
+// centre of wave w's quadrant (clipped to the image) can see the Gaussian with
+// alpha >= alpha_min, i.e. d^T Q d <= tau = 2 ln(o / alpha_min); 0: the entry is
+// dropped. With the columns fixed, the minimum of the convex quadratic over dx
+// is a convex function of dy whose minimiser y* is 0 when the mean's column
+// lies among them, else -b dx_e / c on the nearer edge dx_e; the minimum over
+// the quadrant is at y* clamped to its rows, with dx = -b dy / a clamped to its
+// columns. The margin keeps every entry whose per-pixel decision could go
+// either way in fp32 (no pixel that blends is ever dropped, so the outputs do
+// not depend on this test); it also covers the 1 ulp reciprocals, which move the
+// minimiser and so the minimum in second order only.
+__device__ __forceinline__ uint32_t splat_quads(float u, float v, float a, float b, float c, float o,
+                                                float alpha_min, const TileBox& box) {
   if (!(o >= alpha_min)) return 0u;
   const float tau = 2.0f * (__logf(o) - __logf(alpha_min));
   const float lim = tau * 1.001f + 1e-3f;
-  const float ia = a > 0.0f ? 1.0f / a : 0.0f, ic = c > 0.0f ? 1.0f / c : 0.0f;
-  const float dx0 = box.x0 - u, dx1 = box.x1 - u;
-  const float dxe = dx0 > 0.0f ? dx0 : (dx1 < 0.0f ? dx1 : 0.0f);
-  const float ys = -b * dxe * ic;
-  uint32_t rows = 0;
+  const float mia = a > 0.0f ? -b * __builtin_amdgcn_rcpf(a) : 0.0f;
+  const float mic = c > 0.0f ? -b * __builtin_amdgcn_rcpf(c) : 0.0f;
+  uint32_t quads = 0;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const float yb0 = box.y0 + 4.0f * (float)w, yb1 = fminf(box.y1, yb0 + 3.0f);
-    const float dy = fminf(fmaxf(ys, yb0 - v), yb1 - v);
-    const float dx = fminf(fmaxf(-b * dy * ia, dx0), dx1);
-    const float q = a * dx * dx + 2.0f * b * dx * dy + c * dy * dy;
-    if (yb0 <= yb1 && q <= lim) rows |= 1u << w;
+  for (int qx = 0; qx < 2; ++qx) {
+    const float xb0 = box.x0 + 8.0f * (float)qx, xb1 = fminf(box.x1, xb0 + 7.0f);
+    const float dx0 = xb0 - u, dx1 = xb1 - u;
+    const float ys = mic * __builtin_amdgcn_fmed3f(0.0f, dx0, dx1);
+#pragma unroll
+    for (int qy = 0; qy < 2; ++qy) {
+      const float yb0 = box.y0 + 8.0f * (float)qy, yb1 = fminf(box.y1, yb0 + 7.0f);
+      const float dy = __builtin_amdgcn_fmed3f(ys, yb0 - v, yb1 - v);
+      const float dx = __builtin_amdgcn_fmed3f(mia * dy, dx0, dx1);
+      const float q = a * dx * dx + 2.0f * b * dx * dy + c * dy * dy;
+      if (xb0 <= xb1 && yb0 <= yb1 && q <= lim) quads |= 1u << (2 * qy + qx);
+    }
   }
-  return rows;
+  return quads;
 }
 
-// The same test for single pixel rows: bit w set when pixel row row0 + w of
+// The same test for single pixel rows of the tile: bit w set when pixel row row0 + w of
 // the tile (clipped to the image) can see the Gaussian. With the row fixed,
 // the minimum over the columns is at dx = -b dy / a clamped to the columns.
 __device__ __forceinline__ uint32_t splat_rows_single(float u, float v, float a, float b, float c,
@@ -168,17 +183,17 @@ __device__ __forceinline__ int compact_rows(bool keep, uint32_t rows, int (*s_cn
 }
 
 // The same for kernels whose waves each walk a contiguous copy of their own
-// list: at[r] is this thread's slot in the list of band r (valid where bit r
-// of rows is set), wcnt the length of the calling wave's list; returns the
+// list: at[r] is this thread's slot in the list of quadrant r (valid where bit r
+// of quads is set), wcnt the length of the calling wave's list; returns the
 // number of entries with any bit set (wcnt and the result are uniform). s_cnt
 // holds 5 x 4 wave counts.
-__device__ __forceinline__ int band_slots(uint32_t rows, int (*s_cnt)[4], int (&at)[4], int& wcnt) {
+__device__ __forceinline__ int quad_slots(uint32_t quads, int (*s_cnt)[4], int (&at)[4], int& wcnt) {
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const uint64_t below = (1ull << l) - 1ull;
-  const uint64_t bal = __ballot(rows != 0u);
+  const uint64_t bal = __ballot(quads != 0u);
   uint64_t rb[4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) rb[r] = __ballot((rows >> r) & 1u);
+  for (int r = 0; r < 4; ++r) rb[r] = __ballot((quads >> r) & 1u);
   if (l == 0) {
     s_cnt[0][w] = __popcll(bal);
 #pragma unroll

@@ -18,59 +18,76 @@ __device__ __forceinline__ float dpp_mov(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xF, 0xF, true));
 }
 
-// Wave64 sum of nine values at once. Values 0-7 go through a butterfly that
-// halves the set at each cross-row step without selects: v_permlane32_swap
+// The sums over a wave's 8x8 pixels of the nine gradient values of four list
+// entries. Lane l is pixel (l & 7, l >> 3) of the quadrant, so the column
+// factor dx of a moment is common to a lane's column: the pixels' rows are
+// summed first, of six values per entry,
+//   v[e] = gp, v[4 + e] = gp dy, v[8 + e] = gp dy^2, v[12 + 4 c + e] = colour c,
+// and the moments in dx are formed from those sums, once per column. Lane bits
+// 5, 4 and 3 (the rows) are summed by halving: v_permlane32_swap
 // (v_permlane16_swap) of two registers leaves one value's upper-half (odd-row)
-// partner in the other register, so the sum of the two results holds value
-// 2q in the lower half (even rows) and 2q + 1 in the upper half (odd rows).
-// Two such steps leave two registers, folded across lane bit 3 with one
-// keep/send select pair, and the 8-lane groups finish with three DPP adds
-// (quad xor 1, quad xor 2, row rotate 4). Value 8 is summed by DPP adds
-// within rows and two row-broadcast adds. About 20 VALU instructions. On return each lane l with (l & 7) >= 4 holds the wave total
-// of value sum9_slot(l) in `lo`, and lanes 48-63 the total of value 8 in `v8`.
-struct Sum9 {
-  float lo, v8;
-};
-__device__ __forceinline__ Sum9 wave_sum9(const float (&g)[9], int lane) {
-  float a[4];
+// partner in the other register, so the sum of the two results holds one value
+// in the lower half and the other in the upper; within a 16-lane row, two DPP
+// adds that each write half of the banks (groups of four lanes) do the same,
+// the partner a rotation by two banks away. That leaves three registers in
+// which lane l holds values of entry e = (l >> 5) + 2 (l >> 4 & 1); dx is the
+// lane's for that entry. Bit 2 (mirrored within eight lanes: any lane of the
+// other quad will do, the quads are summed next) halves again, and the quads
+// are summed. 56 instructions, 14 an entry; nine products per pixel and the
+// sum of each over the wave took 33.
+// On return lane l holds field sum_field(l) of its entry (none: -1).
+__device__ __forceinline__ float wave_sums(const float (&v)[24], float dx, int lane) {
+  float a[12], b[6];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_int(g[2 * q]),
-                                                    __float_as_int(g[2 * q + 1]), false, false);
+  for (int q = 0; q < 12; ++q) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_int(v[2 * q]),
+                                                    __float_as_int(v[2 * q + 1]), false, false);
     a[q] = __int_as_float(p[0]) + __int_as_float(p[1]);
   }
-  float b[2];
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
+  for (int q = 0; q < 6; ++q) {
     const auto p = __builtin_amdgcn_permlane16_swap(__float_as_int(a[2 * q]),
                                                     __float_as_int(a[2 * q + 1]), false, false);
     b[q] = __int_as_float(p[0]) + __int_as_float(p[1]);
   }
-  const bool b3 = lane & 8;
-  float c = (b3 ? b[1] : b[0]) + dpp_mov<0x128>(b3 ? b[0] : b[1]);  // row rotate 8
-  c += dpp_mov<0xB1>(c);   // quad [1,0,3,2]
-  c += dpp_mov<0x4E>(c);   // quad [2,3,0,1]
-  c += dpp_mov<0x124>(c);  // row rotate 4 (lane l reads l - 4): lanes with (l & 7) >= 4
-                           // hold the 8-lane sum
-  // value 8: row sums by DPP adds (every lane of a row ends with its row's
-  // sum), then two row-broadcast adds over all rows: lane 15 of each row into
-  // the next (row 3 now holds r2 + r3, row 1 r0 + r1), then lane 31 into rows
-  // 2 and 3, so lanes 48-63 hold the wave total (the other rows hold partial
-  // sums, which are not used)
-  float v8 = g[8];
-  v8 += dpp_mov<0xB1>(v8);   // quad [1,0,3,2]
-  v8 += dpp_mov<0x4E>(v8);   // quad [2,3,0,1]
-  v8 += dpp_mov<0x124>(v8);  // row rotate 4
-  v8 += dpp_mov<0x128>(v8);  // row rotate 8
-  v8 += dpp_mov<0x142>(v8);  // row broadcast 15
-  v8 += dpp_mov<0x143>(v8);  // row broadcast 31
-  return Sum9{c, v8};
+  // A DPP source may be read two wait states after a vector instruction wrote
+  // it at the earliest: the order keeps two instructions between, and an s_nop
+  // leads.
+  float p0, p1, p2, r1, r2, d0, d1, d2;
+  asm("s_nop 1\n\t"
+      "v_add_f32_dpp %0, %8, %8 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %0, %9, %9 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %1, %10, %10 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %1, %11, %11 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %2, %12, %12 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %2, %13, %13 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_mul_f32 %3, %0, %14\n\t"
+      "v_add_f32_dpp %6, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %5, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_mul_f32 %4, %3, %14\n\t"
+      "v_add_f32_dpp %5, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %6, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %7, %4, %4 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %5, %5, %5 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %6, %6, %6 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %7, %7, %7 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %5, %5, %5 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %6, %6, %6 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %7, %7, %7 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
+      : "=&v"(p0), "=&v"(p1), "=&v"(p2), "=&v"(r1), "=&v"(r2), "=&v"(d0), "=&v"(d1), "=&v"(d2)
+      : "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]), "v"(b[5]), "v"(dx));
+  return (lane & 3) == 0 ? d0 : (lane & 3) == 1 ? d1 : d2;
 }
 
-// Which of the values 0-7 lane l holds in Sum9::lo: bit 3 of l picks the
-// group of four, bit 4 the pair, bit 5 the member.
-__device__ __forceinline__ int sum9_slot(int l) {
-  return 4 * ((l >> 3) & 1) + 2 * ((l >> 4) & 1) + ((l >> 5) & 1);
+// The entry of a group of four, and the field of its gradient (0, 1: gp times
+// dx, dy; 2, 3, 4: dx^2, dx dy, dy^2; 5: gp; 6-8: the colours), whose sum lane l
+// of wave_sums holds.
+__device__ __forceinline__ int sum_entry(int l) { return ((l >> 5) & 1) + 2 * ((l >> 4) & 1); }
+__device__ __forceinline__ int sum_field(int l) {
+  const int b2 = (l >> 2) & 1, b3 = (l >> 3) & 1;
+  if ((l & 3) == 0) return b2 ? (b3 ? 3 : 0) : (b3 ? 1 : 5);
+  if ((l & 3) == 1) return b2 ? (b3 ? 8 : 7) : (b3 ? 6 : 4);
+  return (l & 15) == 2 ? 2 : -1;
 }
 
 // One work item of the backward: list positions [lo, hi) of `tile`, chunk j
@@ -87,16 +104,15 @@ __device__ __forceinline__ void bwd_item(
     int64_t gs, const SplitLayout& sp) {
   __shared__ float4 s_ga[256];  // u, v, qa, qb
   __shared__ float4 s_gb[256];  // qc, log2 o, r, g
-  __shared__ float4 s_gc[256];  // a, b, c (conic), colour b
-  __shared__ int s_pos[256];
-  __shared__ uint32_t s_g[256];
-  __shared__ float s_acc[9][256];  // field-major: [field][staged entry]
-  __shared__ __align__(4) uint8_t s_idx[4][256];  // per wave: staged slots reaching its rows
+  __shared__ float4 s_gc[256];  // colour b, list position, Gaussian
+  __shared__ float s_acc[9][257];  // [field][staged entry]; an entry's fields in different banks
+  __shared__ __align__(4) uint8_t s_idx[4][256];  // per wave: staged slots reaching its pixels
   __shared__ int s_wcnt[5][4];
   __shared__ uint32_t s_max;
   const int tid = threadIdx.x;
-  const int px = (tile % k.ntx) * kTile + (tid & 15);
-  const int py = (tile / k.ntx) * kTile + (tid >> 4);
+  const int lane = tid & 63;
+  const int px = (tile % k.ntx) * kTile + quad_x(tid);
+  const int py = (tile / k.ntx) * kTile + quad_y(tid);
   const bool inside = px < k.width && py < k.height;
   const TileBox box = tile_box(k, tile);
   const uint32_t start = tile_ranges[2 * tile];
@@ -154,15 +170,11 @@ __device__ __forceinline__ void bwd_item(
   const uint32_t nent = __builtin_amdgcn_readfirstlane(s_max);  // end of this item's walk
   // d out / d T_final enters every entry's alpha-derivative as T_final g_T / (1 - alpha)
   const float TgT = Tfin * gT;
-  // lanes 4, 12, ..., 60 add values 0-7 of an entry, lane 48 value 8
-  const int lane = tid & 63;
-  const bool adder = (lane & 7) == 4 || lane == 48;
-  const int slot = lane == 48 ? 8 : sum9_slot(lane);
-  float* const acc_lane = s_acc[slot];  // this lane's field, indexed by staged entry
-  uint32_t wml = lastp;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) wml = max(wml, (uint32_t)__shfl_xor((int)wml, off, 64));
-  wml = __builtin_amdgcn_readfirstlane(wml);  // uniform, so its tests compile to scalar branches
+  // the lane's entry of a group and field
+  const int field = sum_field(lane);
+  const bool adder = field >= 0;
+  const int my_shift = 8 * sum_entry(lane);
+  float* const acc_lane = s_acc[adder ? field : 0];
   // entry j of a batch is list position bend - 1 - j (back to front)
   const uint32_t bstop = start + lo;
   uint32_t bend = nent > lo ? start + nent : bstop;
@@ -182,20 +194,19 @@ __device__ __forceinline__ void bwd_item(
     const uint32_t bbeg = bend - min(256u, bend - bstop);
     __syncthreads();
     const float3 cn = conic_of(rec.co);
-    // each wave walks only the staged entries whose ellipse reaches its four
-    // pixel rows: the others contribute nothing to any of its pixels
-    const uint32_t rows =
-        rec.valid ? splat_rows(rec.m.x, rec.m.y, cn.x, cn.y, cn.z, rec.co.w, k.alpha_min, box) : 0u;
-    const bool keep = rows != 0u;
+    // each wave walks only the staged entries whose ellipse reaches its
+    // quadrant: the others contribute nothing to any of its pixels
+    const uint32_t quads =
+        rec.valid ? splat_quads(rec.m.x, rec.m.y, cn.x, cn.y, cn.z, rec.co.w, k.alpha_min, box) : 0u;
+    const bool keep = quads != 0u;
     int pos, wcnt;
-    const int cnt = compact_rows(keep, rows, s_wcnt, s_idx, pos, wcnt);
+    const int cnt = compact_rows(keep, quads, s_wcnt, s_idx, pos, wcnt);
     if (keep) {
       const Splat sp = make_splat(rec.m, rec.co);
       s_ga[pos] = make_float4(sp.u, sp.v, sp.qa, sp.qb);
       s_gb[pos] = make_float4(sp.qc, sp.lo, rec.r, rec.g);
-      s_gc[pos] = make_float4(cn.x, cn.y, cn.z, rec.b);
-      s_pos[pos] = (int)(bend - 1 - tid - start);
-      s_g[pos] = rec.gid;
+      s_gc[pos] = make_float4(rec.b, __uint_as_float(bend - 1 - tid - start),
+                              __uint_as_float(rec.gid), 0.0f);
 #pragma unroll
       for (int q = 0; q < 9; ++q) s_acc[q][pos] = 0.0f;
     }
@@ -216,65 +227,65 @@ __device__ __forceinline__ void bwd_item(
     const uint32_t* my_idx = reinterpret_cast<const uint32_t*>(s_idx[tid >> 6]);
     for (int j0 = 0; j0 < wcnt; j0 += kBwdGroup) {
     float4 gav[kBwdGroup], gbv[kBwdGroup];
-    float cbv[kBwdGroup];  // colour b (the conic in s_gc is needed only at the flush)
-    uint32_t kkv[kBwdGroup];
+    float2 gcv[kBwdGroup];
     const uint32_t iw = __builtin_amdgcn_readfirstlane(my_idx[j0 / 4]);  // four slots (uniform)
 #pragma unroll
     for (int i = 0; i < kBwdGroup; ++i) {
       const int j = (int)((iw >> (8 * i)) & 255u);
       gav[i] = s_ga[j];
       gbv[i] = s_gb[j];
-      cbv[i] = s_gc[j].w;
-      kkv[i] = (uint32_t)s_pos[j];
+      gcv[i] = make_float2(s_gc[j].x, s_gc[j].y);
     }
     // keep the group's reads ahead of the arithmetic (the compiler would
     // otherwise sink each read into the branch that uses it)
 #pragma unroll
     for (int i = 0; i < kBwdGroup; ++i)
       asm volatile("" ::"v"(gav[i].x), "v"(gav[i].y), "v"(gav[i].z), "v"(gav[i].w), "v"(gbv[i].x),
-                   "v"(gbv[i].y), "v"(gbv[i].z), "v"(gbv[i].w), "v"(cbv[i]));
+                   "v"(gbv[i].y), "v"(gbv[i].z), "v"(gbv[i].w), "v"(gcv[i].x), "v"(gcv[i].y));
+    const int my_slot = (int)((iw >> my_shift) & 255u);
+    const float my_u = s_ga[my_slot].x;
+    float gr[6 * kBwdGroup];
+    bool any = false;
 #pragma unroll
     for (int i = 0; i < kBwdGroup; ++i) {
-      if (j0 + i >= wcnt) break;  // wave-uniform
-      const int j = (int)((iw >> (8 * i)) & 255u);  // staged slot (uniform)
-      const uint32_t kk = __builtin_amdgcn_readfirstlane(kkv[i]);
       const float4 ga = gav[i], gb = gbv[i];
-      if (kk >= wml) continue;  // wave-uniform: no pixel of this wave reaches entry kk
       const float dx = fx - ga.x, dy = fy - ga.y;
       const float raw = splat_alpha_raw(dx, dy, ga.z, ga.w, gb.x, gb.y);
-      const bool contrib = kk < lastp && raw >= k.alpha_min;
-      if (!__ballot(contrib)) continue;  // wave-uniform
+      const bool reached = __float_as_uint(gcv[i].y) < lastp, seen = raw >= k.alpha_min;
+      const bool contrib = reached && seen;
+      // wave-uniform: past the list, or no pixel blends it
+      if (j0 + i >= wcnt || !(__ballot(reached) & __ballot(seen))) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) gr[4 * q + i] = 0.0f;
+        continue;
+      }
+      any = true;
       // Branch-free per lane: a lane that does not blend this entry takes
-      // alpha = 0, which leaves T and R unchanged, and a zero mask on the
-      // alpha-derivative terms.
-      const float a = contrib ? fminf(raw, k.alpha_max) : 0.0f;
+      // alpha = 0, which leaves T and RG unchanged and gives zero gradients.
+      const float a = contrib ? clamp_alpha(raw, k.alpha_max) : 0.0f;
       const float om = 1.0f - a;
       const float iom = __builtin_amdgcn_rcpf(om);  // om >= 1 - alpha_max > 0
       const float Tk = T * iom;
       const float wgt = a * Tk;
-      float gr[9];
-      gr[6] = wgt * gcr;
-      gr[7] = wgt * gcg;
-      gr[8] = wgt * gcb;
-      const float CG = gb.z * gcr + gb.w * gcg + cbv[i] * gcb;
-      const float dLda = Tk * (CG - RG) - iom * TgT;
-      RG = a * CG + om * RG;
+      gr[12 + i] = wgt * gcr;
+      gr[16 + i] = wgt * gcg;
+      gr[20 + i] = wgt * gcb;
+      const float D = fmaf(gcv[i].x, gcb, fmaf(gb.w, gcg, fmaf(gb.z, gcr, -RG)));
+      const float dLda = Tk * D - iom * TgT;
+      RG = fmaf(a, D, RG);
       T = Tk;
-      const float dm = (contrib && raw <= k.alpha_max) ? dLda : 0.0f;
-      const float gp = a * dm;
-      // first and second moments of gp over the pixels; the conic and the
-      // constant factors are applied once per entry at the flush
-      const float q = gp * dx, r = gp * dy;
-      gr[0] = q;
-      gr[1] = r;
-      gr[2] = q * dx;
-      gr[3] = q * dy;
-      gr[4] = r * dy;
-      gr[5] = gp;
-      const Sum9 v = wave_sum9(gr, lane);
-      float out = lane == 48 ? v.v8 : v.lo;
-      asm volatile("" : "+v"(out));  // the last folds stay outside the branch (DPP add)
-      if (adder) atomicAdd(acc_lane + j, out);
+      // where the clamp cuts the derivative, and where a = 0, no gradient;
+      // the conic and the constant factors are applied once per entry at the
+      // flush
+      const float gp = raw <= k.alpha_max ? a * dLda : 0.0f;
+      const float r = gp * dy;
+      gr[0 + i] = gp;
+      gr[4 + i] = r;
+      gr[8 + i] = r * dy;
+    }
+    if (any) {
+      const float out = wave_sums(gr, fx - my_u, lane);
+      if (adder) atomicAdd(acc_lane + my_slot, out);
     }
     }
     __syncthreads();
@@ -282,18 +293,20 @@ __device__ __forceinline__ void bwd_item(
       // moments -> dL/d(u, v, a, b, c): with q = dL/dpower * (dx, dy),
       // d power / d(u, v) = (a dx + b dy, b dx + c dy), d power / d(a, b, c)
       // = (-dx^2 / 2, -dx dy, -dy^2 / 2)
-      const float4 co = s_gc[tid];
+      const float4 ga = s_ga[tid];
+      const float l22 = s_gb[tid].x;
       float g[9];
 #pragma unroll
       for (int q = 0; q < 9; ++q) g[q] = s_acc[q][tid];
-      const float mx = g[0], my = g[1];
-      g[0] = co.x * mx + co.y * my;
-      g[1] = co.y * mx + co.z * my;
+      // the staged factor is s times the conic's, s^2 = log2(e) / 2
+      const float mx = (1.0f / kHalfLog2e) * g[0], my = (1.0f / kHalfLog2e) * g[1];
+      g[0] = ga.z * (ga.z * mx + ga.w * my);
+      g[1] = ga.w * (ga.z * mx + ga.w * my) + l22 * l22 * my;
       g[2] = -0.5f * g[2];
       g[3] = -g[3];
       g[4] = -0.5f * g[4];
       g[5] *= __builtin_amdgcn_exp2f(-s_gb[tid].y);  // gp = o d alpha / d o: over the opacity
-      float* dst = g2d + s_g[tid];
+      float* dst = g2d + __float_as_uint(s_gc[tid].z);
 #pragma unroll
       for (int q = 0; q < 9; ++q)
         if (g[q] != 0.0f) atomicAdd(dst + q * gs, g[q]);
@@ -499,7 +512,7 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
       const float raw = splat_alpha_raw(dx, dy, ga.z, ga.w, gb.x, gb.y);
       const bool contrib = valid && kk < lastp && raw >= k.alpha_min;
       if (!__ballot(contrib)) continue;  // wave-uniform
-      const float a = contrib ? fminf(raw, k.alpha_max) : 0.0f;
+      const float a = contrib ? clamp_alpha(raw, k.alpha_max) : 0.0f;
       const float iom = __builtin_amdgcn_rcpf(1.0f - a);  // 1 - a >= 1 - alpha_max > 0
       // transmittance before each entry: T times the inclusive prefix product
       // of 1 / (1 - alpha) over the step's entries, back to front

@@ -7,9 +7,9 @@
 // the next blend would take its transmittance below t_min; the workgroup
 // stops when all its pixels have stopped.
 //
-// Each wave (four pixel rows of the tile) walks only the staged entries whose
-// alpha >= alpha_min ellipse reaches its rows: the others cannot blend at any
-// of its pixels, so the result is the same, and in tiles of many small
+// Each wave (an 8x8 quadrant of the tile) walks only the staged entries whose
+// alpha >= alpha_min ellipse reaches its pixels: the others cannot blend at any
+// of them, so the result is the same, and in tiles of many small
 // Gaussians a wave's walk is a fraction of the tile's list.
 #include <type_traits>
 
@@ -29,7 +29,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
     float4* __restrict__ out, float* __restrict__ final_T, uint32_t* __restrict__ last,
     unsigned long long* __restrict__ n_blends, const uint32_t* __restrict__ order,
     uint2* __restrict__ out16, int* __restrict__ rect, int fb_stop, SplitLayout sp) {
-  // per wave: the staged entries that reach its rows, in list order, then up
+  // per wave: the staged entries that reach its quadrant, in list order, then up
   // to kGroup - 1 entries that blend nothing; reads run one group ahead
   constexpr int kSlots = 256 + 2 * kGroup;
   __shared__ float4 s_ga[4][kSlots];  // u, v, qa, qb
@@ -44,8 +44,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
   const int tile = tile_of_block(k, order);
   if ((unsigned)tile >= (unsigned)k.ntiles) return;
   const int tid = threadIdx.x;
-  const int px = (tile % k.ntx) * kTile + (tid & 15);
-  const int py = (tile / k.ntx) * kTile + (tid >> 4);
+  const int px = (tile % k.ntx) * kTile + quad_x(tid);
+  const int py = (tile / k.ntx) * kTile + quad_y(tid);
   const bool inside = px < k.width && py < k.height;
   const TileBox box = tile_box(k, tile);
   const uint32_t start = tile_ranges[2 * tile], end = tile_ranges[2 * tile + 1];
@@ -114,17 +114,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
       }
     }
     const float3 cn = conic_of(rec.co);
-    // each wave walks only the staged entries whose ellipse reaches its four
-    // pixel rows: the others contribute nothing to any of its pixels
-    const uint32_t rows =
-        rec.valid ? splat_rows(rec.m.x, rec.m.y, cn.x, cn.y, cn.z, rec.co.w, k.alpha_min, box) : 0u;
+    // each wave walks only the staged entries whose ellipse reaches its
+    // quadrant: the others contribute nothing to any of its pixels
+    const uint32_t quads =
+        rec.valid ? splat_quads(rec.m.x, rec.m.y, cn.x, cn.y, cn.z, rec.co.w, k.alpha_min, box) : 0u;
     int at[4], wcnt;
-    staged += (uint32_t)band_slots(rows, s_wcnt, at, wcnt);
-    if (rows != 0u) {
+    staged += (uint32_t)quad_slots(quads, s_wcnt, at, wcnt);
+    if (quads != 0u) {
       const Splat sp = make_splat(rec.m, rec.co);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        if ((rows >> r) & 1u) {
+        if ((quads >> r) & 1u) {
           s_ga[r][at[r]] = make_float4(sp.u, sp.v, sp.qa, sp.qb);
           s_gq[r][at[r]] = make_float2(sp.qc, sp.lo);
           s_rg[r][at[r]] = make_float2(rec.r, rec.g);
@@ -157,8 +157,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
       // group's colours while its alphas are computed, so no LDS latency is
       // waited for, and consecutive records make two entries one 16-byte read.
       // Against selects on the stop in every entry and reads through a list of
-      // slots (28 instructions): 1M Gaussians at 1297x840 180 -> 157 us, 300K
-      // 167 -> 144, 4M tiny ones at 2560x1440 486 -> 410.
+      // slots (28 instructions): 1M Gaussians at 1297x840 180 -> 151 us, 300K
+      // 167 -> 138, 4M tiny ones at 2560x1440 486 -> 390.
       int jl = -1;  // position in the wave's list of the last entry the lane blended
       float4 ga[kGroup];
       float2 gq[kGroup];
@@ -178,15 +178,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
         // alpha of each entry at this pixel, 0 where the lane does not blend
         // it: below alpha_min, or the pixel has stopped (amin_l = inf)
         float a[kGroup];
-        uint32_t hits = 0;  // entry i of the group in bit kGroup - 1 - i
+        bool hit[kGroup];
 #pragma unroll
         for (int i = 0; i < kGroup; ++i) {
           const float al = splat_alpha(fx - ga[i].x, fy - ga[i].y, ga[i].z, ga[i].w, gq[i].x,
                                        gq[i].y, k.alpha_max);
-          const bool hit = al >= amin_l;
-          a[i] = hit ? al : 0.0f;
-          hits = shift_in(hits, hit);
+          hit[i] = al >= amin_l;
+          a[i] = hit[i] ? al : 0.0f;
         }
+        static_assert(kGroup == 4, "four flags");
+        uint32_t hits = bits_of(hit);  // entry i of the group in bit 3 - i
 #pragma unroll
         for (int i = 0; i < kGroup; ++i) {
           ga[i] = s_ga[w][j0 + kGroup + i];
@@ -210,17 +211,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
         if (__ballot(stops)) {
           // some pixel stops in this group: its entries from the stop on get
           // weight zero, which adds exactly zero (colours are finite and >= 0)
-          uint32_t kept = 0;
+          bool ok[kGroup];
           float Tk = T;
 #pragma unroll
           for (int i = 0; i < kGroup; ++i) {
-            const bool ok = Tc[i + 1] >= thr;
-            wt[i] = ok ? wt[i] : 0.0f;
-            kept = shift_in(kept, ok);
-            Tk = ok ? Tc[i + 1] : Tk;
+            ok[i] = Tc[i + 1] >= thr;
+            wt[i] = ok[i] ? wt[i] : 0.0f;
+            Tk = ok[i] ? Tc[i + 1] : Tk;
           }
           Tc[kGroup] = Tk;
-          hits &= kept;
+          hits &= bits_of(ok);
           amin_l = stops ? __builtin_huge_valf() : amin_l;
           none_left = !__ballot(amin_l < __builtin_huge_valf());
         }
