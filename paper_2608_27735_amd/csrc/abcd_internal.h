@@ -107,7 +107,7 @@ __device__ __forceinline__ Splat make_splat(float2 m, float4 co) {
 }
 
 // The conic (a, b, c) = L L^T of a factor (l11, l21, l22): for the tile test
-// (splat_rows) and the chain rule to the mean.
+// (splat_quads) and the chain rule to the mean.
 __device__ __forceinline__ float3 conic_of(float4 co) {
   return make_float3(co.x * co.x, co.x * co.y, co.y * co.y + co.z * co.z);
 }
@@ -270,12 +270,11 @@ int32_t launch_bin_sort(int width, int height, int64_t n, const float* means2d, 
                         uint32_t* tile_ranges, uint32_t* tile_order, hipStream_t stream);
 
 // render_fwd.hip, render_bwd.hip, loss.hip
-// The backward's workspace: the screen-space gradients g2d, field-major
-// (field q of Gaussian i at q * g2d_stride(n) + i, fp32), then per tile the
-// work estimate, the order and the work items (when not split), then the
-// queue counters. Field-major, the nine atomic adds of one Gaussian fall on
-// nine cache lines instead of one or two (adds to one line are serialised in
-// L2); the stride is a multiple of 1024 floats.
+// The backward's workspace: the screen-space gradients g2d[n][9] (fp32, room
+// for n rounded up to a multiple of 1024), then per tile the work estimate,
+// the order and the work items (when not split), then the queue counters. A
+// Gaussian's nine values are consecutive so that one instruction adds them as
+// one or two requests (flush_entries).
 constexpr int64_t g2d_stride(int64_t n) { return (n + 1023) & ~int64_t(1023); }
 constexpr size_t bwd_g2d_bytes(int64_t n) { return (size_t)9 * sizeof(float) * (size_t)g2d_stride(n); }
 constexpr size_t bwd_workspace_bytes(int64_t n) {

@@ -2,9 +2,9 @@
 // gradients reach the active parameters only).
 //
 // The backward walks each pixel's list back to front from its last blended
-// entry, reduces each Gaussian's 9 screen-space gradients across the wave
-// with cross-lane adds, combines the 4 waves in LDS and issues one global
-// fp32 atomic per Gaussian and field per tile.
+// entry, reduces the 9 screen-space gradients of four Gaussians at a time
+// across the wave with cross-lane adds, combines the 4 waves in LDS and adds
+// each Gaussian's nine sums to global memory once per tile.
 #include "blend.h"
 
 namespace abcd {
@@ -90,6 +90,48 @@ __device__ __forceinline__ int sum_field(int l) {
   return (l & 15) == 2 ? 2 : -1;
 }
 
+// Adds the staged entries' gradients to g2d[Gaussian][9] once the workgroup's
+// sums are complete: wave w takes entries 64 w .. of cnt. Each lane first turns
+// its entry's sums into dL/d(u, v, a, b, c, o, r, g, b): with q = gp (dx, dy),
+// d power / d(u, v) = (a dx + b dy, b dx + c dy), d power / d(a, b, c) =
+// (-dx^2 / 2, -dx dy, -dy^2 / 2); ga.zw and gb.x hold the conic's factor times
+// s, s^2 = log2(e) / 2, and gp = o d alpha / d o. Then the wave's lanes add nine
+// consecutive floats of seven Gaussians at a time, so that an entry is one
+// or two requests at the memory side, where the nine adds of one thread were
+// nine: the flush is bound by the rate of atomics to memory that all XCDs
+// share, not by issue (replacing the adds by nothing, or by plain stores, was
+// worth 58 us of 233 on 300K Gaussians at 1297x840 and 310 of 1055 on the
+// heavy-tailed 1M at 1080p; with seven entries an instruction all of it is
+// gained: 163 and 707 us, the 1M block 292 -> 244).
+__device__ __forceinline__ void flush_entries(int cnt, float (*s_acc)[257], const float4* s_ga,
+                                              const float4* s_gb, const float4* s_gc,
+                                              float* __restrict__ g2d) {
+  const int tid = threadIdx.x, lane = tid & 63, e0 = tid & ~63;
+  if (e0 >= cnt) return;  // wave-uniform
+  if (tid < cnt) {
+    const float4 ga = s_ga[tid];
+    const float4 gb = s_gb[tid];
+    const float mx = (1.0f / kHalfLog2e) * s_acc[0][tid], my = (1.0f / kHalfLog2e) * s_acc[1][tid];
+    const float t = ga.z * mx + ga.w * my;
+    s_acc[0][tid] = ga.z * t;
+    s_acc[1][tid] = ga.w * t + gb.x * gb.x * my;
+    s_acc[2][tid] *= -0.5f;
+    s_acc[3][tid] = -s_acc[3][tid];
+    s_acc[4][tid] *= -0.5f;
+    s_acc[5][tid] *= __builtin_amdgcn_exp2f(-gb.y);
+  }
+  const int end = min(cnt, e0 + 64);
+  const int k = lane / 9, f = lane - 9 * k;
+#pragma unroll 2
+  for (int e = e0 + k; e < end + 7; e += 7) {
+    const bool mine = lane < 63 && e < end;
+    const int j = mine ? e : e0;
+    const float g = s_acc[f < 9 ? f : 0][j];
+    const uint32_t gid = __float_as_uint(s_gc[j].z);
+    if (mine && g != 0.0f) atomicAdd(g2d + (uint64_t)gid * 9u + (uint32_t)f, g);
+  }
+}
+
 // One work item of the backward: list positions [lo, hi) of `tile`, chunk j
 // of a split tile (lo = j ch) or the whole walk (j = 0, hi = 2^32 - 1). Each
 // pixel walks the positions below its walk length back to front, starting
@@ -101,7 +143,7 @@ __device__ __forceinline__ void bwd_item(
     const float4* __restrict__ conic_opacity, const float* __restrict__ rgb,
     const float4* __restrict__ F, const float4* __restrict__ B, const float* __restrict__ final_T,
     const uint32_t* __restrict__ last, const float4* __restrict__ dL_dout, float* __restrict__ g2d,
-    int64_t gs, const SplitLayout& sp) {
+    const SplitLayout& sp) {
   __shared__ float4 s_ga[256];  // u, v, qa, qb
   __shared__ float4 s_gb[256];  // qc, log2 o, r, g
   __shared__ float4 s_gc[256];  // colour b, list position, Gaussian
@@ -221,14 +263,19 @@ __device__ __forceinline__ void bwd_item(
     }
     // Entries are read from LDS kGroup at a time, all reads issued before the
     // first is used, so the LDS latency is paid once per group.
-    // The wave's list of staged slots, kBwdGroup at a time; slots past its end
-    // hold stale bytes, which still index the staged arrays.
+    // The wave's list of staged slots, kBwdGroup at a time.
     static_assert(kBwdGroup == 4, "slot indices are read four at a time");
     const uint32_t* my_idx = reinterpret_cast<const uint32_t*>(s_idx[tid >> 6]);
     for (int j0 = 0; j0 < wcnt; j0 += kBwdGroup) {
     float4 gav[kBwdGroup], gbv[kBwdGroup];
     float2 gcv[kBwdGroup];
-    const uint32_t iw = __builtin_amdgcn_readfirstlane(my_idx[j0 / 4]);  // four slots (uniform)
+    // four slots (uniform); past the end of the list the group's first again
+    // (a slot of its own might hold anything, and 0 times a NaN is one)
+    uint32_t iw = __builtin_amdgcn_readfirstlane(my_idx[j0 / 4]);
+    if (j0 + kBwdGroup > wcnt) {
+      const uint32_t keep = 0xFFFFFFFFu >> (8 * (j0 + kBwdGroup - wcnt));
+      iw = (iw & keep) | (((iw & 255u) * 0x01010101u) & ~keep);
+    }
 #pragma unroll
     for (int i = 0; i < kBwdGroup; ++i) {
       const int j = (int)((iw >> (8 * i)) & 255u);
@@ -244,73 +291,55 @@ __device__ __forceinline__ void bwd_item(
                    "v"(gbv[i].y), "v"(gbv[i].z), "v"(gbv[i].w), "v"(gcv[i].x), "v"(gcv[i].y));
     const int my_slot = (int)((iw >> my_shift) & 255u);
     const float my_u = s_ga[my_slot].x;
-    float gr[6 * kBwdGroup];
-    bool any = false;
+    // Per lane and entry: whether the pixel blends it (its walk reached it,
+    // alpha >= alpha_min, and it is not past the end of the wave's list).
+    float raw[kBwdGroup], dy[kBwdGroup];
+    bool contrib[kBwdGroup], free_alpha[kBwdGroup];  // blends it; and not at the clamp
+    uint64_t any = 0;
 #pragma unroll
     for (int i = 0; i < kBwdGroup; ++i) {
-      const float4 ga = gav[i], gb = gbv[i];
-      const float dx = fx - ga.x, dy = fy - ga.y;
-      const float raw = splat_alpha_raw(dx, dy, ga.z, ga.w, gb.x, gb.y);
-      const bool reached = __float_as_uint(gcv[i].y) < lastp, seen = raw >= k.alpha_min;
-      const bool contrib = reached && seen;
-      // wave-uniform: past the list, or no pixel blends it
-      if (j0 + i >= wcnt || !(__ballot(reached) & __ballot(seen))) {
+      const float dx = fx - gav[i].x;
+      dy[i] = fy - gav[i].y;
+      raw[i] = splat_alpha_raw(dx, dy[i], gav[i].z, gav[i].w, gbv[i].x, gbv[i].y);
+      const uint64_t m = __builtin_amdgcn_ballot_w64(__float_as_uint(gcv[i].y) < lastp) &
+                         __builtin_amdgcn_ballot_w64(raw[i] >= k.alpha_min) &
+                         (j0 + i < wcnt ? ~0ull : 0ull);
+      contrib[i] = __builtin_amdgcn_inverse_ballot_w64(m);
+      free_alpha[i] = __builtin_amdgcn_inverse_ballot_w64(
+          m & __builtin_amdgcn_ballot_w64(raw[i] <= k.alpha_max));
+      any |= m;
+    }
+    if (!any) continue;  // wave-uniform
+    // No branch from here on: a lane that does not blend an entry takes alpha
+    // = 0, which leaves T and RG unchanged and gives zero gradients. (Skipping
+    // the entries that no lane of the wave blends, one in five, cost more in
+    // register copies at the joins than it saved.)
+    float gr[6 * kBwdGroup];
 #pragma unroll
-        for (int q = 0; q < 6; ++q) gr[4 * q + i] = 0.0f;
-        continue;
-      }
-      any = true;
-      // Branch-free per lane: a lane that does not blend this entry takes
-      // alpha = 0, which leaves T and RG unchanged and gives zero gradients.
-      const float a = contrib ? clamp_alpha(raw, k.alpha_max) : 0.0f;
-      const float om = 1.0f - a;
-      const float iom = __builtin_amdgcn_rcpf(om);  // om >= 1 - alpha_max > 0
-      const float Tk = T * iom;
-      const float wgt = a * Tk;
+    for (int i = 0; i < kBwdGroup; ++i) {
+      const float a = contrib[i] ? clamp_alpha(raw[i], k.alpha_max) : 0.0f;
+      const float iom = __builtin_amdgcn_rcpf(1.0f - a);  // 1 - a >= 1 - alpha_max > 0
+      T *= iom;  // before the entry
+      const float wgt = a * T;
       gr[12 + i] = wgt * gcr;
       gr[16 + i] = wgt * gcg;
       gr[20 + i] = wgt * gcb;
-      const float D = fmaf(gcv[i].x, gcb, fmaf(gb.w, gcg, fmaf(gb.z, gcr, -RG)));
-      const float dLda = Tk * D - iom * TgT;
+      const float D = fmaf(gcv[i].x, gcb, fmaf(gbv[i].w, gcg, fmaf(gbv[i].z, gcr, -RG)));
+      const float dLda = T * D - iom * TgT;
       RG = fmaf(a, D, RG);
-      T = Tk;
-      // where the clamp cuts the derivative, and where a = 0, no gradient;
-      // the conic and the constant factors are applied once per entry at the
-      // flush
-      const float gp = raw <= k.alpha_max ? a * dLda : 0.0f;
-      const float r = gp * dy;
+      // no gradient where the clamp cuts the derivative; the conic and the
+      // constant factors are applied once per entry at the flush
+      const float gp = free_alpha[i] ? a * dLda : 0.0f;
+      const float r = gp * dy[i];
       gr[0 + i] = gp;
       gr[4 + i] = r;
-      gr[8 + i] = r * dy;
+      gr[8 + i] = r * dy[i];
     }
-    if (any) {
-      const float out = wave_sums(gr, fx - my_u, lane);
-      if (adder) atomicAdd(acc_lane + my_slot, out);
-    }
+    const float out = wave_sums(gr, fx - my_u, lane);
+    if (adder) atomicAdd(acc_lane + my_slot, out);
     }
     __syncthreads();
-    if (tid < cnt) {
-      // moments -> dL/d(u, v, a, b, c): with q = dL/dpower * (dx, dy),
-      // d power / d(u, v) = (a dx + b dy, b dx + c dy), d power / d(a, b, c)
-      // = (-dx^2 / 2, -dx dy, -dy^2 / 2)
-      const float4 ga = s_ga[tid];
-      const float l22 = s_gb[tid].x;
-      float g[9];
-#pragma unroll
-      for (int q = 0; q < 9; ++q) g[q] = s_acc[q][tid];
-      // the staged factor is s times the conic's, s^2 = log2(e) / 2
-      const float mx = (1.0f / kHalfLog2e) * g[0], my = (1.0f / kHalfLog2e) * g[1];
-      g[0] = ga.z * (ga.z * mx + ga.w * my);
-      g[1] = ga.w * (ga.z * mx + ga.w * my) + l22 * l22 * my;
-      g[2] = -0.5f * g[2];
-      g[3] = -g[3];
-      g[4] = -0.5f * g[4];
-      g[5] *= __builtin_amdgcn_exp2f(-s_gb[tid].y);  // gp = o d alpha / d o: over the opacity
-      float* dst = g2d + __float_as_uint(s_gc[tid].z);
-#pragma unroll
-      for (int q = 0; q < 9; ++q)
-        if (g[q] != 0.0f) atomicAdd(dst + q * gs, g[q]);
-    }
+    flush_entries(cnt, s_acc, s_ga, s_gb, s_gc, g2d);
     bend = bbeg;
   }
 }
@@ -322,7 +351,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
     const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
     const float* __restrict__ rgb, const float4* __restrict__ F, const float4* __restrict__ B,
     const float* __restrict__ final_T, const uint32_t* __restrict__ last,
-    const float4* __restrict__ dL_dout, float* __restrict__ g2d, int64_t gs,
+    const float4* __restrict__ dL_dout, float* __restrict__ g2d,
     const uint2* __restrict__ items,
     uint32_t* __restrict__ queue, uint32_t max_items, SplitLayout sp) {
   __shared__ uint2 s_item;
@@ -351,7 +380,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
     if (it.x == kNoSlot) break;
     if (it.x < (uint32_t)k.ntiles)
       bwd_item(k, (int)it.x, it.y, tile_ranges, values, means2d, conic_opacity, rgb, F, B,
-               final_T, last, dL_dout, g2d, gs, sp);
+               final_T, last, dL_dout, g2d, sp);
   }
 }
 
@@ -365,9 +394,9 @@ __global__ __launch_bounds__(256) void render_bwd_direct_kernel(
     const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
     const float* __restrict__ rgb, const float4* __restrict__ F, const float4* __restrict__ B,
     const float* __restrict__ final_T, const uint32_t* __restrict__ last,
-    const float4* __restrict__ dL_dout, float* __restrict__ g2d, int64_t gs) {
+    const float4* __restrict__ dL_dout, float* __restrict__ g2d) {
   bwd_item(k, (int)blockIdx.x, 0u, tile_ranges, values, means2d, conic_opacity, rgb, F, B, final_T,
-           last, dL_dout, g2d, gs, SplitLayout{});
+           last, dL_dout, g2d, SplitLayout{});
 }
 
 // Sums of nine values over each 16-lane row, by a butterfly over lane bits 3
@@ -413,13 +442,11 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
     const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
     const float* __restrict__ rgb, const float4* __restrict__ F, const float4* __restrict__ B,
     const float* __restrict__ final_T, const uint32_t* __restrict__ last,
-    const float4* __restrict__ dL_dout, float* __restrict__ g2d, int64_t gs) {
+    const float4* __restrict__ dL_dout, float* __restrict__ g2d) {
   __shared__ float4 s_ga[256];  // u, v, qa, qb
   __shared__ float4 s_gb[256];  // qc, log2 o, r, g
-  __shared__ float4 s_gc[256];  // a, b, c (conic), colour b
-  __shared__ int s_pos[256];
-  __shared__ uint32_t s_g[256];
-  __shared__ float s_acc[9][256];  // field-major: [field][staged entry]
+  __shared__ float4 s_gc[256];  // colour b, list position, Gaussian
+  __shared__ float s_acc[9][257];  // [field][staged entry]; an entry's fields in different banks
   __shared__ __align__(4) uint8_t s_idx[4][256];  // per wave: staged slots reaching its row
   __shared__ int s_wcnt[5][4];
   __shared__ uint32_t s_max;
@@ -485,9 +512,8 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
       const Splat sp = make_splat(rec.m, rec.co);
       s_ga[pos] = make_float4(sp.u, sp.v, sp.qa, sp.qb);
       s_gb[pos] = make_float4(sp.qc, sp.lo, rec.r, rec.g);
-      s_gc[pos] = make_float4(cn.x, cn.y, cn.z, rec.b);
-      s_pos[pos] = (int)(bend - 1 - tid - start);
-      s_g[pos] = rec.gid;
+      s_gc[pos] = make_float4(rec.b, __uint_as_float(bend - 1 - tid - start),
+                              __uint_as_float(rec.gid), 0.0f);
 #pragma unroll
       for (int q = 0; q < 9; ++q) s_acc[q][pos] = 0.0f;
     }
@@ -505,8 +531,8 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
       const bool valid = j0 + e < wcnt;
       const int j = my_idx[j0 + e];
       const float4 ga = s_ga[j], gb = s_gb[j];
-      const float cb = s_gc[j].w;
-      const uint32_t kk = (uint32_t)s_pos[j];
+      const float cb = s_gc[j].x;
+      const uint32_t kk = __float_as_uint(s_gc[j].y);
       if (!__ballot(valid && kk < wml)) continue;  // wave-uniform
       const float dx = fx - ga.x, dy = fy - ga.y;
       const float raw = splat_alpha_raw(dx, dy, ga.z, ga.w, gb.x, gb.y);
@@ -555,23 +581,7 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
       if (adder && valid) atomicAdd(&s_acc[slot][j], out);
     }
     __syncthreads();
-    if (tid < cnt) {
-      const float4 co = s_gc[tid];
-      float g[9];
-#pragma unroll
-      for (int q = 0; q < 9; ++q) g[q] = s_acc[q][tid];
-      const float mx = g[0], my = g[1];
-      g[0] = co.x * mx + co.y * my;
-      g[1] = co.y * mx + co.z * my;
-      g[2] = -0.5f * g[2];
-      g[3] = -g[3];
-      g[4] = -0.5f * g[4];
-      g[5] *= __builtin_amdgcn_exp2f(-s_gb[tid].y);  // gp = o d alpha / d o: over the opacity
-      float* dst = g2d + s_g[tid];
-#pragma unroll
-      for (int q = 0; q < 9; ++q)
-        if (g[q] != 0.0f) atomicAdd(dst + q * gs, g[q]);
-    }
+    flush_entries(cnt, s_acc, s_ga, s_gb, s_gc, g2d);
     bend = bbeg;
   }
 }
@@ -621,13 +631,13 @@ int32_t launch_render_bwd_pixels(const abcd_camera& cam, const abcd_raster_param
                   tile_ranges, values_sorted, reinterpret_cast<const float2*>(means2d),
                   reinterpret_cast<const float4*>(conic_opacity), rgb,
                   reinterpret_cast<const float4*>(F), reinterpret_cast<const float4*>(B), final_T,
-                  last, reinterpret_cast<const float4*>(dL_dout), g2d, g2d_stride(n));
+                  last, reinterpret_cast<const float4*>(dL_dout), g2d);
     else
       ABCD_LAUNCH("render_bwd", render_bwd_direct_kernel, k.ntiles, kBlock, 0, stream, k,
                   tile_ranges, values_sorted, reinterpret_cast<const float2*>(means2d),
                   reinterpret_cast<const float4*>(conic_opacity), rgb,
                   reinterpret_cast<const float4*>(F), reinterpret_cast<const float4*>(B), final_T,
-                  last, reinterpret_cast<const float4*>(dL_dout), g2d, g2d_stride(n));
+                  last, reinterpret_cast<const float4*>(dL_dout), g2d);
     ABCD_HIP(hipGetLastError());
     return ABCD_OK;
   }
@@ -654,7 +664,7 @@ int32_t launch_render_bwd_pixels(const abcd_camera& cam, const abcd_raster_param
               values_sorted, reinterpret_cast<const float2*>(means2d),
               reinterpret_cast<const float4*>(conic_opacity), rgb,
               reinterpret_cast<const float4*>(F), reinterpret_cast<const float4*>(B), final_T,
-              last, reinterpret_cast<const float4*>(dL_dout), g2d, g2d_stride(n), items, queue,
+              last, reinterpret_cast<const float4*>(dL_dout), g2d, items, queue,
               max_items, split);
   ABCD_HIP(hipGetLastError());
   return ABCD_OK;
