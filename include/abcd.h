@@ -407,7 +407,7 @@ ABCD_API int32_t abcd_adam_step(const abcd_adam_group* groups /* host */, int32_
  * on the caller's stream). abcd_timing_read synchronises, and returns the
  * accumulated milliseconds and launch count of the kernel named `kernel`
  * (names: composite, project, bin_zero, depth_keys, radix_pass, l1_place,
- * l2_count, l2_scatter, bin_small_sort, bin_small_collect, bin_empty,
+ * l2_count, l2_scatter, bin_small_sort, bin_small_collect, bin_empty, bin_count,
  * render_fwd, loss_l1, zero_fill, bwd_order, render_bwd, project_bwd, adam,
  * render_cache, cache_rect_init). */
 ABCD_API const char* abcd_last_error(void);

@@ -131,3 +131,22 @@ def test_backward_upstream_nan_stays_local(api, size):
         assert np.isfinite(g[~listed]).all(), k
         # the order of the atomic adds differs between the two calls
         assert np.linalg.norm(g[~listed] - c[~listed]) <= 1e-5 * np.linalg.norm(c), k
+
+
+@pytest.mark.parametrize("n", [2048, 2049, 4099, 300_001])
+def test_binning_without_capacity_counts(api, n):
+    """A call with no capacity leaves the intersection count of a full call, empty
+    ranges and the identity order, on both sides of the small-block path."""
+    from paper_2608_27735_amd.camera import RasterParams, look_at
+    r = S.rng(600 + n)
+    cam = look_at((0.2, -3.0, 0.9), (0, 0, 0), 203, 117)
+    sc = S.gaussians(r, r.uniform(-2, 2, (n, 3)), 0, np.log(0.02), 0.6)
+    say("no capacity", n)
+    proj = api.project(cam, RasterParams(sh_degree=0),
+                       **{k: torch.from_numpy(v).to(dev()) for k, v in sc.items()})
+    full = api.bin_sort(cam.width, cam.height, proj)
+    got = api.bin_sort(cam.width, cam.height, proj, capacity=0, sync=False)
+    assert api.intersections(got["workspace"]) == full["n_isect"]
+    assert full["n_isect"] == int(proj["tiles_touched"].sum())
+    assert int(got["tile_ranges"].abs().max()) == 0
+    assert torch.equal(got["tile_order"].cpu(), torch.arange(len(got["tile_order"]), dtype=torch.int32))
