@@ -63,6 +63,8 @@ constexpr int kBlk = 8;                     // block side in tiles
 constexpr int kBlkTiles = kBlk * kBlk;
 constexpr int kCountGrid = 512;             // workgroups of the grid-stride level-2 count
 constexpr int kScatterGrid = 8192;          // workgroups of the grid-stride level-2 scatter
+constexpr int kRangeParts = 1024;           // most workgroups that look for the keys' range
+constexpr int kRangeItems = 8;              // Gaussians per thread of one of them, or more
 
 struct WsHeader {
   unsigned long long m;   // intersections (sum of tiles_touched)
@@ -73,7 +75,8 @@ struct WsHeader {
   uint32_t ticket_l1;     // chunks taken by l1_place
   uint32_t done_l2;       // blocks whose level-2 scan is done
   uint32_t nonempty;      // blocks holding at least one entry
-  uint32_t pad[51];
+  uint32_t passes;        // radix passes that the keys' range needs (1 to 4)
+  uint32_t pad[50];
 };
 static_assert(sizeof(WsHeader) == 256, "header is one 256-byte slot");
 
@@ -94,7 +97,7 @@ inline Geo geo_of(int width, int height) {
 }
 
 struct WsLayout {
-  size_t hdr, ghist, mcopy, bcopy, blk_done, lb1, st0, st1, keys_a, keys_b, vals_a, vals_b, rects, blk_off,
+  size_t range, hdr, ghist, mcopy, bcopy, blk_done, lb1, st0, st1, keys_a, keys_b, vals_a, vals_b, rects, blk_off,
       sub_off, slice_off, pairs, c2, slice_tot, tile_total, tile_off, total;
   int64_t rs_parts, chunks, max_sub, max_slices;
 };
@@ -126,6 +129,7 @@ WsLayout ws_layout(int64_t n, int64_t capacity, const Geo& g) {
   L.st1 = take(sizeof(unsigned long long) * 256 * L.rs_parts);
   L.keys_a = take(sizeof(uint32_t) * n);
   L.keys_b = take(sizeof(uint32_t) * n);
+  L.range = take(2 * sizeof(uint32_t) * kRangeParts);
   L.vals_a = take(sizeof(uint32_t) * n);
   L.vals_b = take(sizeof(uint32_t) * n);
   L.rects = take(sizeof(unsigned long long) * n);
@@ -185,10 +189,52 @@ __device__ __forceinline__ unsigned long long pack_rect(int x0, int y0, int x1, 
 
 // Clears the header (with the radix passes' tickets), the digit counts and
 // the first pass's partition states: one contiguous region of 16-byte words.
-__global__ __launch_bounds__(256) void bin_zero_kernel(uint4* __restrict__ p, int64_t words) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words;
+// Beside that, workgroup b < parts looks for the smallest and the largest depth
+// (fp32 bits) of its share of the Gaussians with any tile, into range[b] and
+// range[kRangeParts + b] (0xffffffff and 0 for none): keys counted from the
+// smallest need fewer digits, a radix pass less for each 8 bits.
+__global__ __launch_bounds__(256) void bin_zero_kernel(uint4* __restrict__ p, int64_t words,
+                                                       int64_t n,
+                                                       const float* __restrict__ depth,
+                                                       const uint32_t* __restrict__ tiles,
+                                                       int parts, uint32_t* __restrict__ range) {
+  __shared__ uint32_t s_lo[4], s_hi[4];
+  const int tid = threadIdx.x;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + tid; i < words;
        i += (int64_t)gridDim.x * blockDim.x)
     p[i] = make_uint4(0u, 0u, 0u, 0u);
+  if ((int)blockIdx.x >= parts) return;
+  uint32_t lo = 0xffffffffu, hi = 0u;
+  const int64_t stride = (int64_t)parts * kBlock;
+  for (int64_t i0 = (int64_t)blockIdx.x * kBlock + tid; i0 < n; i0 += kRangeItems * stride) {
+    uint32_t t[kRangeItems], d[kRangeItems];
+#pragma unroll
+    for (int k = 0; k < kRangeItems; ++k) {
+      const int64_t i = min(i0 + k * stride, n - 1);  // past the end: the last again
+      t[k] = tiles[i];
+      d[k] = __float_as_uint(depth[i]);
+    }
+#pragma unroll
+    for (int k = 0; k < kRangeItems; ++k)
+      if (t[k] != 0u) {
+        lo = min(lo, d[k]);
+        hi = max(hi, d[k]);
+      }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, off, 64));
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, off, 64));
+  }
+  if ((tid & 63) == 0) {
+    s_lo[tid >> 6] = lo;
+    s_hi[tid >> 6] = hi;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    range[blockIdx.x] = min(min(s_lo[0], s_lo[1]), min(s_lo[2], s_lo[3]));
+    range[kRangeParts + blockIdx.x] = max(max(s_hi[0], s_hi[1]), max(s_hi[2], s_hi[3]));
+  }
 }
 
 // Adds this wave's keys to the workgroup's counts h[4][256] of each digit
@@ -211,8 +257,9 @@ __device__ __forceinline__ void count_digits(uint32_t (*h)[256], uint32_t key, b
   }
 }
 
-// Depth keys (fp32 bits; a Gaussian with no tile gets 0xffffffff and sorts
-// last), packed tile rectangles, and, added into copy blockIdx mod
+// Depth keys (fp32 bits less the smallest; a Gaussian with no tile gets the
+// largest plus one and sorts last), the number of radix passes they need,
+// packed tile rectangles, and, added into copy blockIdx mod
 // kHistCopies (cleared before the launch): the counts of each value of each
 // of the four key digits (ghist[copy][digit][value]), the Gaussians covering
 // each 8x8-tile block (bcopy[copy][block]; s_blk: 4 x geo.nblk words of
@@ -223,11 +270,21 @@ __global__ __launch_bounds__(256) void depth_keys_kernel(
     const float* __restrict__ means2d, const float* __restrict__ extent, Geo geo,
     uint32_t* __restrict__ keys, unsigned long long* __restrict__ rects,
     uint32_t* __restrict__ ghist, uint32_t* __restrict__ bcopy,
-    unsigned long long* __restrict__ mcopy) {
+    unsigned long long* __restrict__ mcopy, int parts, const uint32_t* __restrict__ range,
+    WsHeader* __restrict__ hdr) {
   extern __shared__ uint32_t s_blk[];
   __shared__ uint32_t h[4][256];
   __shared__ unsigned long long s_m;
+  __shared__ uint32_t s_lo[4], s_hi[4];
   const int tid = threadIdx.x;
+  // the range of the visible keys (while the Gaussians are on their way)
+  uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+  for (int k = 0; k < kRangeParts / kBlock; ++k) {
+    const int b = k * kBlock + tid;
+    lo = min(lo, b < parts ? range[b] : 0xffffffffu);
+    hi = max(hi, b < parts ? range[kRangeParts + b] : 0u);
+  }
 #pragma unroll
   for (int b = 0; b < 4; ++b) h[b][tid] = 0;
   for (int b = tid; b < 4 * geo.nblk; b += kBlock) s_blk[b] = 0;
@@ -247,14 +304,30 @@ __global__ __launch_bounds__(256) void depth_keys_kernel(
     mm[it] = ok ? reinterpret_cast<const float2*>(means2d)[i] : make_float2(0.0f, 0.0f);
     ee[it] = ok ? reinterpret_cast<const float2*>(extent)[i] : make_float2(0.0f, 0.0f);
   }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, off, 64));
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, off, 64));
+  }
+  if ((tid & 63) == 0) {
+    s_lo[tid >> 6] = lo;
+    s_hi[tid >> 6] = hi;
+  }
   __syncthreads();
+  lo = min(min(s_lo[0], s_lo[1]), min(s_lo[2], s_lo[3]));
+  hi = max(max(s_hi[0], s_hi[1]), max(s_hi[2], s_hi[3]));
+  // no visible Gaussian, or a depth that is not positive: keys from 0
+  if (lo > hi) lo = hi = 0u;
+  if (hi >= 0x80000000u) lo = 0u, hi = 0xfffffffeu;
+  const uint32_t none = hi - lo + 1u;  // after every visible key
+  if (blockIdx.x == 0 && tid == 0) hdr->passes = (uint32_t)((32 - __clz(none) + 7) / 8);
   uint32_t m = 0;  // at most kDkItems x 32768 tiles
 #pragma unroll
   for (int it = 0; it < kDkItems; ++it) {
     const int64_t i = base + it * kBlock + tid;
     const bool ok = i < n;
     const bool vis = ok && tt[it] != 0;
-    const uint32_t key = vis ? __float_as_uint(dp[it]) : 0xffffffffu;
+    const uint32_t key = vis ? __float_as_uint(dp[it]) - lo : none;
     int x0 = 1, y0 = 0, x1 = 0, y1 = 0;
     const bool hit = vis && tile_rect(mm[it].x, mm[it].y, ee[it].x, ee[it].y, geo.ntx, geo.nty, x0,
                                       y0, x1, y1);
@@ -370,7 +443,9 @@ __global__ __launch_bounds__(256) void radix_pass_kernel(
     const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in, int64_t n, int pass,
     const uint32_t* __restrict__ ghist, unsigned long long* __restrict__ st,
     unsigned long long* __restrict__ st_next, uint32_t* __restrict__ ticket,
-    uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out) {
+    const uint32_t* __restrict__ passes, uint32_t* __restrict__ keys_out,
+    uint32_t* __restrict__ vals_out) {
+  if (pass >= (int)*passes) return;  // every key's digit is 0
   constexpr int kPerWave = kRsTile / 4;
   constexpr int kWaveItems = kPerWave / 64;
   __shared__ uint32_t s_key[kRsTile];
@@ -549,13 +624,15 @@ __device__ __forceinline__ uint32_t slices_of(uint32_t s0, uint32_t s1) {
 }
 
 __global__ __launch_bounds__(256) void l1_place_kernel(
-    int64_t n, const uint32_t* __restrict__ order, const unsigned long long* __restrict__ rects,
-    Geo geo, const uint32_t* __restrict__ bcopy, const unsigned long long* __restrict__ mcopy,
+    int64_t n, const uint32_t* __restrict__ order_even, const uint32_t* __restrict__ order_odd,
+    const unsigned long long* __restrict__ rects, Geo geo, const uint32_t* __restrict__ bcopy, const unsigned long long* __restrict__ mcopy,
     unsigned long long capacity, int64_t chunks, uint32_t* __restrict__ lb,
     uint32_t* __restrict__ blk_off, uint32_t* __restrict__ sub_off, uint32_t* __restrict__ slice_off,
     WsHeader* __restrict__ hdr, unsigned long long* __restrict__ pairs,
     uint32_t* __restrict__ tile_total) {
   using SW = StateWord<uint32_t>;
+  // where the last radix pass left the order
+  const uint32_t* __restrict__ order = (hdr->passes & 1u) ? order_odd : order_even;
   extern __shared__ uint32_t lds[];
   uint32_t* slot = lds;                    // [4][nblk]: per wave counts, then next free slots
   uint32_t* boff = lds + 4 * geo.nblk;     // [nblk]: block totals, then bucket offsets
@@ -1478,10 +1555,15 @@ int32_t launch_bin_sort(int width, int height, int64_t n, const float* means2d, 
                                    reinterpret_cast<unsigned long long*>(ws + L.st1)};
   uint32_t* ghist = u32(L.ghist);
   unsigned long long* rects = reinterpret_cast<unsigned long long*>(ws + L.rects);
+  uint32_t* range = u32(L.range);
+  const int parts = (int)std::min<int64_t>(
+      kRangeParts, (n + kBlock * kRangeItems - 1) / (kBlock * kRangeItems));
   {
     const int64_t words = (int64_t)(L.st1 - L.hdr) / 16;
-    ABCD_LAUNCH("bin_zero", bin_zero_kernel, std::min<int64_t>(1024, (words + kBlock - 1) / kBlock),
-                kBlock, 0, stream, reinterpret_cast<uint4*>(ws + L.hdr), words);
+    ABCD_LAUNCH("bin_zero", bin_zero_kernel,
+                std::max<int64_t>(parts, std::min<int64_t>(1024, (words + kBlock - 1) / kBlock)),
+                kBlock, 0, stream, reinterpret_cast<uint4*>(ws + L.hdr), words, n, depth,
+                tiles_touched, parts, range);
   }
   static bool attrs_set = false;
   if (!attrs_set) {
@@ -1499,16 +1581,14 @@ int32_t launch_bin_sort(int width, int height, int64_t n, const float* means2d, 
   unsigned long long* mcopy = reinterpret_cast<unsigned long long*>(ws + L.mcopy);
   ABCD_LAUNCH("depth_keys", depth_keys_kernel, (n + kDkTile - 1) / kDkTile, kBlock,
               4 * sizeof(uint32_t) * geo.nblk, stream, n, depth, tiles_touched, means2d, extent, geo,
-              keys[0], rects, ghist, bcopy, mcopy);
+              keys[0], rects, ghist, bcopy, mcopy, parts, range, hdr);
   for (int pass = 0; pass < 4; ++pass) {
     const int src = pass & 1, dst = src ^ 1;
     ABCD_LAUNCH("radix_pass", radix_pass_kernel, L.rs_parts, kBlock, 0, stream, keys[src],
                 pass == 0 ? nullptr : vals[src], n, pass, ghist, pstate[pass & 1],
-                pass < 3 ? pstate[(pass + 1) & 1] : nullptr, &hdr->ticket[pass], keys[dst],
-                vals[dst]);
+                pass < 3 ? pstate[(pass + 1) & 1] : nullptr, &hdr->ticket[pass], &hdr->passes,
+                keys[dst], vals[dst]);
   }
-  const uint32_t* order = vals[0];  // four passes: back in buffer 0
-
   const unsigned long long cap = (unsigned long long)std::max<int64_t>(capacity, 0);
   uint32_t* blk_off = u32(L.blk_off);
   uint32_t* sub_off = u32(L.sub_off);
@@ -1519,7 +1599,7 @@ int32_t launch_bin_sort(int width, int height, int64_t n, const float* means2d, 
   uint32_t* slice_off = u32(L.slice_off);
   uint32_t* slice_tot = u32(L.slice_tot);
   ABCD_LAUNCH("l1_place", l1_place_kernel, L.chunks, kBlock, 5 * sizeof(uint32_t) * geo.nblk,
-              stream, n, order, rects, geo, bcopy, mcopy, cap, L.chunks, u32(L.lb1), blk_off,
+              stream, n, vals[0], vals[1], rects, geo, bcopy, mcopy, cap, L.chunks, u32(L.lb1), blk_off,
               sub_off, slice_off, hdr, pairs, tile_total);
   ABCD_LAUNCH("l2_count", l2_count_kernel, kCountGrid, 64 * kSlice, 0, stream, pairs, geo, sub_off,
               slice_off, blk_off, hdr, c2, slice_tot, u32(L.blk_done), tile_total, tile_off,
