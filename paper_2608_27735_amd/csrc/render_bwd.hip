@@ -132,6 +132,17 @@ __device__ __forceinline__ void flush_entries(int cnt, float (*s_acc)[257], cons
   }
 }
 
+// Workgroup memory of the backward kernels.
+struct BwdLds {
+  float4 ga[256];     // u, v, qa, qb
+  float4 gb[256];     // qc, log2 o, r, g
+  float4 gc[256];     // colour b, list position, Gaussian
+  float acc[9][257];  // [field][staged entry]; an entry's fields in different banks
+  __align__(4) uint8_t idx[4][256];  // per wave: staged slots reaching its pixels
+  int wcnt[5][4];
+  uint32_t max;
+};
+
 // One work item of the backward: list positions [lo, hi) of `tile`, chunk j
 // of a split tile (lo = j ch) or the whole walk (j = 0, hi = 2^32 - 1). Each
 // pixel walks the positions below its walk length back to front, starting
@@ -140,19 +151,12 @@ __device__ __forceinline__ void flush_entries(int cnt, float (*s_acc)[257], cons
 // pixels).
 template <bool kDirect>
 __device__ __forceinline__ void bwd_item(
-    const BlendConsts& k, int tile, uint32_t j, const uint32_t* __restrict__ tile_ranges,
+    BwdLds& s, const BlendConsts& k, int tile, uint32_t j, const uint32_t* __restrict__ tile_ranges,
     const uint32_t* __restrict__ values, const float2* __restrict__ means2d,
     const float4* __restrict__ conic_opacity, const float* __restrict__ rgb,
     const float4* __restrict__ F, const float4* __restrict__ B, const float* __restrict__ final_T,
     const uint32_t* __restrict__ last, const float4* __restrict__ dL_dout, const uint32_t* __restrict__ walk, float* __restrict__ g2d,
     const SplitLayout& sp) {
-  __shared__ float4 s_ga[256];  // u, v, qa, qb
-  __shared__ float4 s_gb[256];  // qc, log2 o, r, g
-  __shared__ float4 s_gc[256];  // colour b, list position, Gaussian
-  __shared__ float s_acc[9][257];  // [field][staged entry]; an entry's fields in different banks
-  __shared__ __align__(4) uint8_t s_idx[4][256];  // per wave: staged slots reaching its pixels
-  __shared__ int s_wcnt[5][4];
-  __shared__ uint32_t s_max;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int px = (tile % k.ntx) * kTile + quad_x(tid);
@@ -184,11 +188,11 @@ __device__ __forceinline__ void bwd_item(
                            : (int64_t)(tile / k.ntx) * kTile * k.width + (tile % k.ntx) * kTile;
   const uint32_t lastp = inside ? last[p] : 0u;
   if (kDirect) {
-    if (tid == 0) s_max = 0;
+    if (tid == 0) s.max = 0;
     __syncthreads();
-    if (lastp) atomicMax(&s_max, lastp);
+    if (lastp) atomicMax(&s.max, lastp);
     __syncthreads();
-    nent = __builtin_amdgcn_readfirstlane(s_max);
+    nent = __builtin_amdgcn_readfirstlane(s.max);
   }
   nent = min(nent, hi);
   // entry j of a batch is list position bend - 1 - j (back to front)
@@ -236,7 +240,7 @@ __device__ __forceinline__ void bwd_item(
   const int field = sum_field(lane);
   const bool adder = field >= 0;
   const int my_shift = 8 * sum_entry(lane);
-  float* const acc_lane = s_acc[adder ? field : 0];
+  float* const acc_lane = s.acc[adder ? field : 0];
   while (bend > bstop) {
     const uint32_t bbeg = bend - min(256u, bend - bstop);
     __syncthreads();
@@ -247,15 +251,15 @@ __device__ __forceinline__ void bwd_item(
         rec.valid ? splat_quads(rec.m.x, rec.m.y, cn.x, cn.y, cn.z, rec.co.w, k.alpha_min, box) : 0u;
     const bool keep = quads != 0u;
     int pos, wcnt;
-    const int cnt = compact_rows(keep, quads, s_wcnt, s_idx, pos, wcnt);
+    const int cnt = compact_rows(keep, quads, s.wcnt, s.idx, pos, wcnt);
     if (keep) {
-      const Splat sp = make_splat(rec.m, rec.co);
-      s_ga[pos] = make_float4(sp.u, sp.v, sp.qa, sp.qb);
-      s_gb[pos] = make_float4(sp.qc, sp.lo, rec.r, rec.g);
-      s_gc[pos] = make_float4(rec.b, __uint_as_float(bend - 1 - tid - start),
+      const Splat g = make_splat(rec.m, rec.co);
+      s.ga[pos] = make_float4(g.u, g.v, g.qa, g.qb);
+      s.gb[pos] = make_float4(g.qc, g.lo, rec.r, rec.g);
+      s.gc[pos] = make_float4(rec.b, __uint_as_float(bend - 1 - tid - start),
                               __uint_as_float(rec.gid), 0.0f);
 #pragma unroll
-      for (int q = 0; q < 9; ++q) s_acc[q][pos] = 0.0f;
+      for (int q = 0; q < 9; ++q) s.acc[q][pos] = 0.0f;
     }
     __syncthreads();
     {
@@ -270,7 +274,7 @@ __device__ __forceinline__ void bwd_item(
     // first is used, so the LDS latency is paid once per group.
     // The wave's list of staged slots, kBwdGroup at a time.
     static_assert(kBwdGroup == 4, "slot indices are read four at a time");
-    const uint32_t* my_idx = reinterpret_cast<const uint32_t*>(s_idx[tid >> 6]);
+    const uint32_t* my_idx = reinterpret_cast<const uint32_t*>(s.idx[tid >> 6]);
     for (int j0 = 0; j0 < wcnt; j0 += kBwdGroup) {
     float4 gav[kBwdGroup], gbv[kBwdGroup];
     float2 gcv[kBwdGroup];
@@ -284,9 +288,9 @@ __device__ __forceinline__ void bwd_item(
 #pragma unroll
     for (int i = 0; i < kBwdGroup; ++i) {
       const int j = (int)((iw >> (8 * i)) & 255u);
-      gav[i] = s_ga[j];
-      gbv[i] = s_gb[j];
-      gcv[i] = make_float2(s_gc[j].x, s_gc[j].y);
+      gav[i] = s.ga[j];
+      gbv[i] = s.gb[j];
+      gcv[i] = make_float2(s.gc[j].x, s.gc[j].y);
     }
     // keep the group's reads ahead of the arithmetic (the compiler would
     // otherwise sink each read into the branch that uses it)
@@ -295,7 +299,7 @@ __device__ __forceinline__ void bwd_item(
       asm volatile("" ::"v"(gav[i].x), "v"(gav[i].y), "v"(gav[i].z), "v"(gav[i].w), "v"(gbv[i].x),
                    "v"(gbv[i].y), "v"(gbv[i].z), "v"(gbv[i].w), "v"(gcv[i].x), "v"(gcv[i].y));
     const int my_slot = (int)((iw >> my_shift) & 255u);
-    const float my_u = s_ga[my_slot].x;
+    const float my_u = s.ga[my_slot].x;
     // Per lane and entry: whether the pixel blends it (its walk reached it,
     // alpha >= alpha_min, and it is not past the end of the wave's list).
     float raw[kBwdGroup], dy[kBwdGroup];
@@ -344,7 +348,7 @@ __device__ __forceinline__ void bwd_item(
     if (adder) atomicAdd(acc_lane + my_slot, out);
     }
     __syncthreads();
-    flush_entries(cnt, s_acc, s_ga, s_gb, s_gc, g2d);
+    flush_entries(cnt, s.acc, s.ga, s.gb, s.gc, g2d);
     bend = bbeg;
   }
 }
@@ -361,6 +365,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
     const float4* __restrict__ dL_dout, const uint32_t* __restrict__ walk, float* __restrict__ g2d,
     const uint2* __restrict__ items,
     uint32_t* __restrict__ queue, uint32_t max_items, SplitLayout sp) {
+  __shared__ BwdLds s;
   __shared__ uint2 s_item;
   const uint32_t n_items = min(queue[0], max_items);
   // Atomic adds to one address are serialised, and light items at the end
@@ -375,7 +380,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
   uint2 it = blockIdx.x < n_items ? items[blockIdx.x] : make_uint2(kNoSlot, 0u);
   while (it.x != kNoSlot) {  // uniform
     if (it.x < (uint32_t)k.ntiles)
-      bwd_item<false>(k, (int)it.x, it.y, tile_ranges, values, means2d, conic_opacity, rgb, F, B,
+      bwd_item<false>(s, k, (int)it.x, it.y, tile_ranges, values, means2d, conic_opacity, rgb, F, B,
                       final_T, last, dL_dout, walk, g2d, sp);
     if (threadIdx.x == 0) {
       const uint32_t r = gq + atomicAdd(&queue[kQueueStride * q + 1], 1u);
@@ -390,20 +395,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void r
   }
 }
 
-// Small frames (few tiles, no split): one workgroup per tile in raster order,
-// without the schedule's two launches (the launch-bound regime of small
-// active partitions).
 constexpr int kDirectTiles = 1024;
-
-__global__ __launch_bounds__(256) void render_bwd_direct_kernel(
-    BlendConsts k, const uint32_t* __restrict__ tile_ranges, const uint32_t* __restrict__ values,
-    const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
-    const float* __restrict__ rgb, const float4* __restrict__ F, const float4* __restrict__ B,
-    const float* __restrict__ final_T, const uint32_t* __restrict__ last,
-    const float4* __restrict__ dL_dout, float* __restrict__ g2d) {
-  bwd_item<true>(k, (int)blockIdx.x, 0u, tile_ranges, values, means2d, conic_opacity, rgb, F, B,
-                 final_T, last, dL_dout, nullptr, g2d, SplitLayout{});
-}
+static_assert(kDirectTiles <= kFewTiles, "the direct kernel asks for the pairs");
 
 // Sums of nine values over each 16-lane row, by a butterfly over lane bits 3
 // (row rotate 8), 2 (half-row mirror, which pairs lanes whose bit 2 differs),
@@ -443,19 +436,13 @@ __device__ __forceinline__ int rowsum9_slot(int c) {
 // alpha T (c . g), not normalised by the transmittance, so that the
 // alpha-derivative is T (c . g) - (S + T_final g_T) / (1 - alpha).
 
-__global__ __launch_bounds__(256) void render_bwd_rows_kernel(
-    BlendConsts k, const uint32_t* __restrict__ tile_ranges, const uint32_t* __restrict__ values,
+__device__ __forceinline__ void bwd_rows(
+    BwdLds& s, const BlendConsts& k, const uint32_t* __restrict__ tile_ranges,
+    const uint32_t* __restrict__ values,
     const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
     const float* __restrict__ rgb, const float4* __restrict__ F, const float4* __restrict__ B,
     const float* __restrict__ final_T, const uint32_t* __restrict__ last,
     const float4* __restrict__ dL_dout, float* __restrict__ g2d) {
-  __shared__ float4 s_ga[256];  // u, v, qa, qb
-  __shared__ float4 s_gb[256];  // qc, log2 o, r, g
-  __shared__ float4 s_gc[256];  // colour b, list position, Gaussian
-  __shared__ float s_acc[9][257];  // [field][staged entry]; an entry's fields in different banks
-  __shared__ __align__(4) uint8_t s_idx[4][256];  // per wave: staged slots reaching its row
-  __shared__ int s_wcnt[5][4];
-  __shared__ uint32_t s_max;
   const int tile = (int)(blockIdx.x >> 2), quarter = (int)(blockIdx.x & 3);
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, e = lane >> 4;
   const int px = (tile % k.ntx) * kTile + col;
@@ -466,7 +453,7 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
   const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
   float T = 1.0f, gcr = 0, gcg = 0, gcb = 0, gT = 0;
   uint32_t lastp = 0;
-  if (tid == 0) s_max = 0;
+  if (tid == 0) s.max = 0;
   __syncthreads();
   if (inside) {
     const int64_t p = (int64_t)py * k.width + px;
@@ -475,15 +462,15 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
     const float4 G = dL_dout[p];
     const float4 f = F ? F[p] : make_float4(0, 0, 0, 0);
     const float4 bb = B ? B[p] : make_float4(0, 0, 0, 0);
-    const float s = 1.0f - f.w;
-    gcr = s * G.x;
-    gcg = s * G.y;
-    gcb = s * G.z;
-    gT = s * (G.x * bb.x + G.y * bb.y + G.z * bb.z - G.w * (1.0f - bb.w));
-    if (lastp > 0u) atomicMax(&s_max, lastp);
+    const float sf = 1.0f - f.w;
+    gcr = sf * G.x;
+    gcg = sf * G.y;
+    gcb = sf * G.z;
+    gT = sf * (G.x * bb.x + G.y * bb.y + G.z * bb.z - G.w * (1.0f - bb.w));
+    if (lastp > 0u) atomicMax(&s.max, lastp);
   }
   __syncthreads();
-  const uint32_t nent = __builtin_amdgcn_readfirstlane(s_max);  // end of the quarter's walk
+  const uint32_t nent = __builtin_amdgcn_readfirstlane(s.max);  // end of the quarter's walk
   const float TgT = T * gT;  // T is the final transmittance here
   float S = 0.0f;            // colour behind the step (sum of alpha T (c . g))
   uint32_t wml = lastp;
@@ -513,15 +500,15 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
                                     : 0u;
     const bool keep = rows != 0u;
     int pos, wcnt;
-    const int cnt = compact_rows(keep, rows, s_wcnt, s_idx, pos, wcnt);
+    const int cnt = compact_rows(keep, rows, s.wcnt, s.idx, pos, wcnt);
     if (keep) {
       const Splat sp = make_splat(rec.m, rec.co);
-      s_ga[pos] = make_float4(sp.u, sp.v, sp.qa, sp.qb);
-      s_gb[pos] = make_float4(sp.qc, sp.lo, rec.r, rec.g);
-      s_gc[pos] = make_float4(rec.b, __uint_as_float(bend - 1 - tid - start),
+      s.ga[pos] = make_float4(sp.u, sp.v, sp.qa, sp.qb);
+      s.gb[pos] = make_float4(sp.qc, sp.lo, rec.r, rec.g);
+      s.gc[pos] = make_float4(rec.b, __uint_as_float(bend - 1 - tid - start),
                               __uint_as_float(rec.gid), 0.0f);
 #pragma unroll
-      for (int q = 0; q < 9; ++q) s_acc[q][pos] = 0.0f;
+      for (int q = 0; q < 9; ++q) s.acc[q][pos] = 0.0f;
     }
     __syncthreads();
     {
@@ -531,14 +518,23 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
       gid_next = gid_after;
     }
     // slots past the end of the wave's list hold stale bytes: they still index
-    // the staged arrays, and their lanes take part in nothing below
-    const uint8_t* my_idx = s_idx[tid >> 6];
+    // the staged arrays, and their lanes take part in nothing below. The next
+    // step's entries, and the slots of the one after, are read while a step is
+    // worked on.
+    const uint8_t* my_idx = s.idx[tid >> 6];
+    int jn = my_idx[e], jn2 = my_idx[4 + e];
+    float4 gan = s.ga[jn], gbn = s.gb[jn], gcn = s.gc[jn];
     for (int j0 = 0; j0 < wcnt; j0 += 4) {
       const bool valid = j0 + e < wcnt;
-      const int j = my_idx[j0 + e];
-      const float4 ga = s_ga[j], gb = s_gb[j];
-      const float cb = s_gc[j].x;
-      const uint32_t kk = __float_as_uint(s_gc[j].y);
+      const int j = jn;
+      const float4 ga = gan, gb = gbn;
+      const float cb = gcn.x;
+      const uint32_t kk = __float_as_uint(gcn.y);
+      jn = jn2;
+      jn2 = my_idx[min(j0 + 8 + e, 255)];
+      gan = s.ga[jn];
+      gbn = s.gb[jn];
+      gcn = s.gc[jn];
       if (!__ballot(valid && kk < wml)) continue;  // wave-uniform
       const float dx = fx - ga.x, dy = fy - ga.y;
       const float raw = splat_alpha_raw(dx, dy, ga.z, ga.w, gb.x, gb.y);
@@ -584,12 +580,40 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
       const float m = row_sum9(gr, col, v8);
       float out = col == 1 ? v8 : m;
       asm volatile("" : "+v"(out));  // the last folds stay outside the branch (DPP add)
-      if (adder && valid) atomicAdd(&s_acc[slot][j], out);
+      if (adder && valid) atomicAdd(&s.acc[slot][j], out);
     }
     __syncthreads();
-    flush_entries(cnt, s_acc, s_ga, s_gb, s_gc, g2d);
+    flush_entries(cnt, s.acc, s.ga, s.gb, s.gc, g2d);
     bend = bbeg;
   }
+}
+
+__global__ __launch_bounds__(256) void render_bwd_rows_kernel(
+    BlendConsts k, const uint32_t* __restrict__ tile_ranges, const uint32_t* __restrict__ values,
+    const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
+    const float* __restrict__ rgb, const float4* __restrict__ F, const float4* __restrict__ B,
+    const float* __restrict__ final_T, const uint32_t* __restrict__ last,
+    const float4* __restrict__ dL_dout, float* __restrict__ g2d) {
+  __shared__ BwdLds s;
+  bwd_rows(s, k, tile_ranges, values, means2d, conic_opacity, rgb, F, B, final_T, last, dL_dout, g2d);
+}
+
+// Unsplit frames of at most kDirectTiles tiles, without the schedule's two
+// launches: one workgroup per tile in raster order, or, with few pairs, four
+// (see kFewPairs).
+__global__ __launch_bounds__(256) void render_bwd_direct_kernel(
+    BlendConsts k, const uint32_t* __restrict__ tile_ranges, const uint32_t* __restrict__ values,
+    const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
+    const float* __restrict__ rgb, const float4* __restrict__ F, const float4* __restrict__ B,
+    const float* __restrict__ final_T, const uint32_t* __restrict__ last,
+    const float4* __restrict__ dL_dout, float* __restrict__ g2d) {
+  __shared__ BwdLds s;
+  if (tile_ranges[2 * k.ntiles - 1] <= kFewPairs)
+    bwd_rows(s, k, tile_ranges, values, means2d, conic_opacity, rgb, F, B, final_T, last, dL_dout,
+             g2d);
+  else if ((int)blockIdx.x < k.ntiles)
+    bwd_item<true>(s, k, (int)blockIdx.x, 0u, tile_ranges, values, means2d, conic_opacity, rgb, F, B,
+                   final_T, last, dL_dout, nullptr, g2d, SplitLayout{});
 }
 
 }  // namespace
@@ -639,7 +663,7 @@ int32_t launch_render_bwd_pixels(const abcd_camera& cam, const abcd_raster_param
                   reinterpret_cast<const float4*>(F), reinterpret_cast<const float4*>(B), final_T,
                   last, reinterpret_cast<const float4*>(dL_dout), g2d);
     else
-      ABCD_LAUNCH("render_bwd", render_bwd_direct_kernel, k.ntiles, kBlock, 0, stream, k,
+      ABCD_LAUNCH("render_bwd", render_bwd_direct_kernel, 4 * k.ntiles, kBlock, 0, stream, k,
                   tile_ranges, values_sorted, reinterpret_cast<const float2*>(means2d),
                   reinterpret_cast<const float4*>(conic_opacity), rgb,
                   reinterpret_cast<const float4*>(F), reinterpret_cast<const float4*>(B), final_T,

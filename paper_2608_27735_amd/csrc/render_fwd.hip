@@ -18,29 +18,258 @@
 namespace abcd {
 namespace {
 
+// Workgroup memory of the forward kernels: per wave, the staged entries that
+// reach its pixels, in list order, then up to kGroup - 1 entries that blend
+// nothing; reads run one group ahead.
+constexpr int kSlots = 256 + 2 * kGroup;
+struct FwdLds {
+  float4 ga[4][kSlots];  // u, v, qa, qb
+  float2 gq[4][kSlots];  // qc, log2 o
+  float2 rg[4][kSlots];  // r, g
+  float bl[4][kSlots];   // b
+  uint8_t at[4][256];    // position in the batch
+  int wcnt[5][4];
+  unsigned long long nb;
+  uint32_t base;
+  uint32_t walk;  // largest walk of the tile (split only)
+};
+
+// Stages one batch: the thread's entry `rec` (at position tid of the batch) into
+// the lists of the waves w whose bit of `reach` is set, and the padding of the
+// wave's own list. Returns the number of entries with any bit set and the
+// length of the wave's list; ends with a barrier.
+__device__ __forceinline__ int stage_fwd(FwdLds& s, const Rec& rec, uint32_t reach, int& wcnt) {
+  const int tid = threadIdx.x, w = tid >> 6;
+  int at[4];
+  const int kept = quad_slots(reach, s.wcnt, at, wcnt);
+  if (reach != 0u) {
+    const Splat sp = make_splat(rec.m, rec.co);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if ((reach >> r) & 1u) {
+        s.ga[r][at[r]] = make_float4(sp.u, sp.v, sp.qa, sp.qb);
+        s.gq[r][at[r]] = make_float2(sp.qc, sp.lo);
+        s.rg[r][at[r]] = make_float2(rec.r, rec.g);
+        s.bl[r][at[r]] = rec.b;
+        s.at[r][at[r]] = (uint8_t)tid;
+      }
+    }
+  }
+  if ((tid & 63) < kGroup) {  // the last group's rest: alpha 2^-1e30 = 0
+    const int p = wcnt + (tid & 63);
+    s.ga[w][p] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    s.gq[w][p] = make_float2(0.0f, -1e30f);
+    s.rg[w][p] = make_float2(0.0f, 0.0f);
+    s.bl[w][p] = 0.0f;
+  }
+  __syncthreads();
+  return kept;
+}
+
+// Small frames (at most kRowsTiles tiles, no split): four workgroups per
+// tile (rows 4q .. 4q + 3 for quarter q), one pixel row per wave and four
+// list entries per step of a wave, as in the backward for small frames. Lane
+// l holds column l & 15 of the wave's row and entry l >> 4 of the step (entry
+// 0 the frontmost). Per step, the transmittance before and after each entry
+// is the running chain T times an exclusive and an inclusive prefix product of
+// 1 - alpha over the step's entries (scans over lane bits 4 and 5). The
+// inclusive products never increase along the step (each is a rounded product
+// of the one before and a factor at most 1), so an entry blends exactly when
+// its product is still at or above the threshold, and the first entry that
+// fails stops the pixel. Each lane sums the colour, blend count and walk end
+// of its own entries; the four rows are combined once, at the end (the
+// pixel's transmittance is the smallest of the rows' last blended values).
+template <bool kHalf>
+__device__ __forceinline__ void fwd_rows(
+    FwdLds& s, const BlendConsts& k, const uint32_t* __restrict__ tile_ranges, const uint32_t* __restrict__ values,
+    const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
+    const float* __restrict__ rgb, const float4* __restrict__ F, const float4* __restrict__ B,
+    float4* __restrict__ out, float* __restrict__ final_T, uint32_t* __restrict__ last,
+    unsigned long long* __restrict__ n_blends, uint2* __restrict__ out16, int* __restrict__ rect,
+    int fb_stop, const SplitLayout& sp) {
+  const int tile = (int)(blockIdx.x >> 2), quarter = (int)(blockIdx.x & 3);
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, col = lane & 15, e = lane >> 4;
+  const int px = (tile % k.ntx) * kTile + col;
+  const int py = (tile / k.ntx) * kTile + 4 * quarter + (tid >> 6);
+  const bool inside = px < k.width && py < k.height;
+  const TileBox box = tile_box(k, tile);
+  const uint32_t start = tile_ranges[2 * tile], end = tile_ranges[2 * tile + 1];
+  const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
+  bool done = !inside;
+  float thr = k.t_min;  // stop threshold on the next transmittance (see render_fwd_kernel)
+  if (!kHalf && fb_stop && F && inside) {
+    const float vis = 1.0f - F[(int64_t)py * k.width + px].w;
+    thr = vis > 0.0f ? k.t_min / vis : __builtin_huge_valf();
+    done = vis < k.t_min;
+  }
+  float amin_l = done ? __builtin_huge_valf() : fmaxf(k.alpha_min, __FLT_DENORM_MIN__);
+  float T = 1.0f;      // the pixel's chain through the steps so far (same in its four lanes)
+  float Tlast = 1.0f;  // the chain after this lane's last entry that passed the threshold
+  float cr = 0.0f, cg = 0.0f, cb = 0.0f;
+  uint32_t lastk = 0, nb = 0;
+  const bool odd = lane & 16, high = lane & 32;
+  if (tid == 0) s.nb = 0;
+  const uint32_t lastpos = end > start ? end - 1 : start;
+  Rec rec{};
+  uint32_t gid_next = 0;
+  if (end > start) {  // uniform
+    const uint32_t gid0 = values[min(start + tid, lastpos)];
+    gid_next = values[min(start + 256 + tid, lastpos)];
+    rec = gather_rec(gid0, start + tid < end, means2d, conic_opacity, rgb);
+  }
+  for (uint32_t b0 = start; b0 < end; b0 += 256) {
+    if (__syncthreads_count(done) == 256) break;
+    const float3 cn = conic_of(rec.co);
+    const uint32_t rows = rec.valid ? splat_rows_single(rec.m.x, rec.m.y, cn.x, cn.y, cn.z,
+                                                        rec.co.w, k.alpha_min, box, 4 * quarter)
+                                    : 0u;
+    int wcnt;
+    stage_fwd(s, rec, rows, wcnt);
+    const uint32_t nxt = b0 + 256 + tid;
+    const uint32_t gid_after = values[min(b0 + 512 + tid, lastpos)];
+    rec = gather_rec(gid_next, nxt < end, means2d, conic_opacity, rgb);
+    gid_next = gid_after;
+    if (__ballot(!done)) {
+      // a step's four entries, one per 16 lanes; the next step's are read while
+      // this one blends
+      int jl = -1;  // position in the wave's list of the lane's last blended entry
+      float4 ga = s.ga[w][e];
+      float2 gq = s.gq[w][e], rg = s.rg[w][e];
+      float bl = s.bl[w][e];
+      for (int j0 = 0; j0 < wcnt; j0 += 4) {
+        const int jw = j0 + e;
+        const float al = splat_alpha(fx - ga.x, fy - ga.y, ga.z, ga.w, gq.x, gq.y, k.alpha_max);
+        const float2 rg0 = rg;
+        const float bl0 = bl;
+        ga = s.ga[w][jw + 4];
+        gq = s.gq[w][jw + 4];
+        rg = s.rg[w][jw + 4];
+        bl = s.bl[w][jw + 4];
+        // 0 where the lane blends nothing: past the list, below alpha_min, or
+        // the pixel has stopped
+        const float a = al >= amin_l ? al : 0.0f;
+        const float om = 1.0f - a;
+        const Swapped p1 = swap_bit4(om);
+        const float t1 = p1.first * p1.second;
+        const Swapped p2 = swap_bit5(t1);
+        const float in1 = odd ? t1 : om, ex1 = odd ? p1.first : 1.0f;
+        const float Tn = T * (high ? in1 * p2.first : in1);  // after the entry
+        const float Tc = T * (high ? ex1 * p2.first : ex1);  // before it
+        const bool ok = Tn >= thr;
+        // a zero weight adds exactly zero (colours are finite and >= 0)
+        const float wgt = ok ? a * Tc : 0.0f;
+        cr = fmaf(rg0.x, wgt, cr);
+        cg = fmaf(rg0.y, wgt, cg);
+        cb = fmaf(bl0, wgt, cb);
+        const bool blend = ok && a != 0.0f;
+        jl = blend ? jw : jl;
+        nb += blend ? 1u : 0u;
+        Tlast = ok ? Tn : Tlast;
+        T *= p2.first * p2.second;  // through the step's four entries
+        done = done || T < thr;
+        amin_l = done ? __builtin_huge_valf() : amin_l;
+        if (!__ballot(!done)) break;  // wave-uniform
+      }
+      if (jl >= 0) lastk = (b0 - start) + (uint32_t)s.at[w][jl] + 1u;
+    }
+    // s_wcnt is rewritten only after the next barrier
+  }
+  // combine the pixel's four lanes
+  {
+    const Swapped r1 = swap_bit4(cr), g1 = swap_bit4(cg), c1 = swap_bit4(cb), t1 = swap_bit4(Tlast);
+    const Swapped r2 = swap_bit5(r1.first + r1.second), g2 = swap_bit5(g1.first + g1.second),
+                  c2 = swap_bit5(c1.first + c1.second), t2 = swap_bit5(fminf(t1.first, t1.second));
+    cr = r2.first + r2.second;
+    cg = g2.first + g2.second;
+    cb = c2.first + c2.second;
+    T = fminf(t2.first, t2.second);
+    const Swapped k1 = swap_bit4(__uint_as_float(lastk));
+    const uint32_t l1 = max(__float_as_uint(k1.first), __float_as_uint(k1.second));
+    const Swapped k2 = swap_bit5(__uint_as_float(l1));
+    lastk = max(__float_as_uint(k2.first), __float_as_uint(k2.second));
+  }
+  if (!kHalf && sp.ckpt) {
+    // no tile is split; its walk and work estimate are the largest of the
+    // quarters' (cleared before the launch)
+    uint32_t m = lastk;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
+    if (lane == 0 && m) {
+      atomicMax(&sp.walk[tile], m);
+      atomicMax(&sp.work[tile], m);
+    }
+    if (quarter == 0 && tid == 0) sp.slot_of[(size_t)tile * kMaxChunks] = kNoSlot;
+  }
+  if (kHalf && rect) {
+    // coverage of the cached image: tiles holding any pixel that blended
+    if (__syncthreads_or(inside && T < 1.0f) && tid == 0) {
+      const int tx = tile % k.ntx, ty = tile / k.ntx;
+      atomicMin(&rect[0], tx * kTile);
+      atomicMin(&rect[1], ty * kTile);
+      atomicMax(&rect[2], min(tx * kTile + kTile, k.width));
+      atomicMax(&rect[3], min(ty * kTile + kTile, k.height));
+    }
+  }
+  if (inside && e == 0) {
+    const int64_t p = (int64_t)py * k.width + px;
+    if (kHalf) {
+      const _Float16 h[4] = {(_Float16)cr, (_Float16)cg, (_Float16)cb, (_Float16)(1.0f - T)};
+      out16[p] = __builtin_bit_cast(uint2, h);
+    } else {
+      const float4 f = F ? F[p] : make_float4(0, 0, 0, 0);
+      const float4 bb = B ? B[p] : make_float4(0, 0, 0, 0);
+      const float s = 1.0f - f.w;
+      out[p] = make_float4(f.x + s * (cr + T * bb.x), f.y + s * (cg + T * bb.y),
+                           f.z + s * (cb + T * bb.z), f.w + s * (1.0f - T * (1.0f - bb.w)));
+      final_T[p] = T;
+      last[p] = lastk;
+    }
+  }
+  if (n_blends) {
+    const unsigned long long wsum = wave_sum_u32(nb);
+    __syncthreads();
+    if (lane == 0) atomicAdd(&s.nb, wsum);
+    __syncthreads();
+    if (tid == 0 && s.nb) atomicAdd(n_blends, s.nb);
+  }
+}
+
+template <bool kHalf>
+__global__ __launch_bounds__(256) void render_fwd_rows_kernel(
+    BlendConsts k, const uint32_t* __restrict__ tile_ranges, const uint32_t* __restrict__ values,
+    const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
+    const float* __restrict__ rgb, const float4* __restrict__ F, const float4* __restrict__ B,
+    float4* __restrict__ out, float* __restrict__ final_T, uint32_t* __restrict__ last,
+    unsigned long long* __restrict__ n_blends, uint2* __restrict__ out16, int* __restrict__ rect,
+    int fb_stop) {
+  __shared__ FwdLds s;
+  fwd_rows<kHalf>(s, k, tile_ranges, values, means2d, conic_opacity, rgb, F, B, out, final_T, last,
+                  n_blends, out16, rect, fb_stop, SplitLayout{});
+}
+
 // kHalf: the cached-render variant: F = B = transparent, the image is written
 // as fp16 RGBA to out16 (round to nearest even), no final T or walk lengths.
+// kFew: a frame that may take the rows layout (see kFewPairs); few is then the
+// number of workgroups of the general one. (In the one kernel for all frames the
+// extra code cost the large ones 2%.)
 // Register budget: four waves per SIMD (at most 128 VGPRs).
-template <bool kHalf>
+template <bool kHalf, bool kFew>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void render_fwd_kernel(
     BlendConsts k, const uint32_t* __restrict__ tile_ranges, const uint32_t* __restrict__ values,
     const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
     const float* __restrict__ rgb, const float4* __restrict__ F, const float4* __restrict__ B,
     float4* __restrict__ out, float* __restrict__ final_T, uint32_t* __restrict__ last,
     unsigned long long* __restrict__ n_blends, const uint32_t* __restrict__ order,
-    uint2* __restrict__ out16, int* __restrict__ rect, int fb_stop, SplitLayout sp) {
-  // per wave: the staged entries that reach its quadrant, in list order, then up
-  // to kGroup - 1 entries that blend nothing; reads run one group ahead
-  constexpr int kSlots = 256 + 2 * kGroup;
-  __shared__ float4 s_ga[4][kSlots];  // u, v, qa, qb
-  __shared__ float2 s_gq[4][kSlots];  // qc, log2 o
-  __shared__ float2 s_rg[4][kSlots];  // r, g
-  __shared__ float s_bl[4][kSlots];   // b
-  __shared__ uint8_t s_at[4][256];    // position in the batch
-  __shared__ int s_wcnt[5][4];
-  __shared__ unsigned long long s_nb;
-  __shared__ uint32_t s_base;
-  __shared__ uint32_t s_walk;  // largest walk of the tile (split only)
+    uint2* __restrict__ out16, int* __restrict__ rect, int fb_stop, SplitLayout sp, int few) {
+  __shared__ FwdLds s;
+  if (kFew) {
+    if (tile_ranges[2 * k.ntiles - 1] <= kFewPairs) {  // the number of pairs
+      fwd_rows<kHalf>(s, k, tile_ranges, values, means2d, conic_opacity, rgb, F, B, out, final_T,
+                      last, n_blends, out16, rect, fb_stop, sp);
+      return;
+    }
+    if ((int)blockIdx.x >= few) return;
+  }
   const int tile = tile_of_block(k, order);
   if ((unsigned)tile >= (unsigned)k.ntiles) return;
   const int tid = threadIdx.x;
@@ -67,8 +296,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
   // the pixel has stopped
   float amin_l = done ? __builtin_huge_valf() : fmaxf(k.alpha_min, __FLT_DENORM_MIN__);
   if (tid == 0) {
-    s_nb = 0;
-    s_walk = 0;
+    s.nb = 0;
+    s.walk = 0;
   }
   // Checkpoints for the split backward (uniform state): a slot per boundary
   // the walk crosses, taken when it crosses
@@ -99,11 +328,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
       // the loop did not reach
       if (tid == 0) {
         const uint32_t got = atomicAdd(&sp.hdr[0], 1u);
-        s_base = got < sp.nslots ? got : kNoSlot;
-        sp.slot_of[(size_t)tile * kMaxChunks + (b0 - start) / chd] = s_base;
+        s.base = got < sp.nslots ? got : kNoSlot;
+        sp.slot_of[(size_t)tile * kMaxChunks + (b0 - start) / chd] = s.base;
       }
       __syncthreads();
-      const uint32_t slot = s_base;
+      const uint32_t slot = s.base;
       if (slot == kNoSlot) {
         split_ok = false;  // out of slots: the backward takes this tile whole
       } else {
@@ -118,30 +347,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
     // quadrant: the others contribute nothing to any of its pixels
     const uint32_t quads =
         rec.valid ? splat_quads(rec.m.x, rec.m.y, cn.x, cn.y, cn.z, rec.co.w, k.alpha_min, box) : 0u;
-    int at[4], wcnt;
-    staged += (uint32_t)quad_slots(quads, s_wcnt, at, wcnt);
-    if (quads != 0u) {
-      const Splat sp = make_splat(rec.m, rec.co);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if ((quads >> r) & 1u) {
-          s_ga[r][at[r]] = make_float4(sp.u, sp.v, sp.qa, sp.qb);
-          s_gq[r][at[r]] = make_float2(sp.qc, sp.lo);
-          s_rg[r][at[r]] = make_float2(rec.r, rec.g);
-          s_bl[r][at[r]] = rec.b;
-          s_at[r][at[r]] = (uint8_t)tid;
-        }
-      }
-    }
+    int wcnt;
+    staged += (uint32_t)stage_fwd(s, rec, quads, wcnt);
     const int w = tid >> 6;
-    if ((tid & 63) < kGroup) {  // the last group's rest: alpha 2^-1e30 = 0
-      const int p = wcnt + (tid & 63);
-      s_ga[w][p] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      s_gq[w][p] = make_float2(0.0f, -1e30f);
-      s_rg[w][p] = make_float2(0.0f, 0.0f);
-      s_bl[w][p] = 0.0f;
-    }
-    __syncthreads();
     // gathers of the next batch and list values of the one after overlap the
     // blend of this one
     const uint32_t nxt = b0 + 256 + tid;
@@ -164,16 +372,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
       float2 gq[kGroup];
 #pragma unroll
       for (int i = 0; i < kGroup; ++i) {
-        ga[i] = s_ga[w][i];
-        gq[i] = s_gq[w][i];
+        ga[i] = s.ga[w][i];
+        gq[i] = s.gq[w][i];
       }
       for (int j0 = 0; j0 < wcnt; j0 += kGroup) {
         float2 rg[kGroup];
         float bl[kGroup];
 #pragma unroll
         for (int i = 0; i < kGroup; ++i) {
-          rg[i] = s_rg[w][j0 + i];
-          bl[i] = s_bl[w][j0 + i];
+          rg[i] = s.rg[w][j0 + i];
+          bl[i] = s.bl[w][j0 + i];
         }
         // alpha of each entry at this pixel, 0 where the lane does not blend
         // it: below alpha_min, or the pixel has stopped (amin_l = inf)
@@ -190,8 +398,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
         uint32_t hits = bits_of(hit);  // entry i of the group in bit 3 - i
 #pragma unroll
         for (int i = 0; i < kGroup; ++i) {
-          ga[i] = s_ga[w][j0 + kGroup + i];
-          gq[i] = s_gq[w][j0 + kGroup + i];
+          ga[i] = s.ga[w][j0 + kGroup + i];
+          gq[i] = s.gq[w][j0 + kGroup + i];
         }
         // The chain Tc of every hit blended, T (1 - alpha) with one rounding
         // (exactly T where alpha = 0), holds the values of the entry-by-entry
@@ -235,30 +443,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
         jl = hits ? j0 + kGroup - __ffs((int)hits) : jl;
         if (none_left) break;  // wave-uniform
       }
-      if (jl >= 0) lastk = (b0 - start) + (uint32_t)s_at[w][jl] + 1u;
+      if (jl >= 0) lastk = (b0 - start) + (uint32_t)s.at[w][jl] + 1u;
     }
-    // s_wcnt is rewritten only after the next barrier
+    // s.wcnt is rewritten only after the next barrier
   }
   if (cht != 0u) {
     // the tile's largest walk, for the backward's schedule
     uint32_t wmax = lastk;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) wmax = max(wmax, (uint32_t)__shfl_xor((int)wmax, off, 64));
-    if ((tid & 63) == 0 && wmax) atomicMax(&s_walk, wmax);
-    __syncthreads();  // every thread has read s_base; s_walk is complete
+    if ((tid & 63) == 0 && wmax) atomicMax(&s.walk, wmax);
+    __syncthreads();  // every thread has read s.base; s.walk is complete
     if (tid == 0) {
-      sp.walk[tile] = s_walk;
+      sp.walk[tile] = s.walk;
       uint32_t fin = kNoSlot;
       if (split_ok && crossed) {
         const uint32_t got = atomicAdd(&sp.hdr[0], 1u);
         if (got < sp.nslots) fin = got;
       }
-      s_base = fin;
+      s.base = fin;
       sp.slot_of[(size_t)tile * kMaxChunks] = fin;
       sp.work[tile] = min(max(staged_max, staged), kSplitTile - 1u) | (fin != kNoSlot ? kSplitTile : 0u);
     }
     __syncthreads();
-    const uint32_t slot = s_base;
+    const uint32_t slot = s.base;
     if (slot != kNoSlot) sp.ckpt[(size_t)slot * 256 + tid] = make_float4(T, cr, cg, cb);
   }
   if (kHalf && rect) {
@@ -289,177 +497,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
   if (n_blends) {
     const unsigned long long wsum = wave_sum_u32(nb);
     __syncthreads();
-    if ((tid & 63) == 0) atomicAdd(&s_nb, wsum);
+    if ((tid & 63) == 0) atomicAdd(&s.nb, wsum);
     __syncthreads();
-    if (tid == 0 && s_nb) atomicAdd(n_blends, s_nb);
+    if (tid == 0 && s.nb) atomicAdd(n_blends, s.nb);
   }
 }
 
-// Small frames (at most kRowsTiles tiles, no split): four workgroups per
-// tile (rows 4q .. 4q + 3 for quarter q), one pixel row per wave and four
-// list entries per step of a wave, as in the backward for small frames. Lane
-// l holds column l & 15 of the wave's row and entry l >> 4 of the step (entry
-// 0 the frontmost). Per step, the transmittance before and after each entry
-// is the running chain T times an exclusive and an inclusive prefix product of
-// 1 - alpha over the step's entries (scans over lane bits 4 and 5). The
-// inclusive products never increase along the step (each is a rounded product
-// of the one before and a factor at most 1), so an entry blends exactly when
-// its product is still at or above the threshold, and the first entry that
-// fails stops the pixel. Each lane sums the colour, blend count and walk end
-// of its own entries; the four rows are combined once, at the end (the
-// pixel's transmittance is the smallest of the rows' last blended values).
-template <bool kHalf>
-__global__ __launch_bounds__(256) void render_fwd_rows_kernel(
-    BlendConsts k, const uint32_t* __restrict__ tile_ranges, const uint32_t* __restrict__ values,
-    const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
-    const float* __restrict__ rgb, const float4* __restrict__ F, const float4* __restrict__ B,
-    float4* __restrict__ out, float* __restrict__ final_T, uint32_t* __restrict__ last,
-    unsigned long long* __restrict__ n_blends, uint2* __restrict__ out16, int* __restrict__ rect,
-    int fb_stop) {
-  __shared__ float4 s_ga[256];  // u, v, qa, qb
-  __shared__ float4 s_gb[256];  // qc, log2 o, r, g
-  __shared__ float s_bl[256];   // b
-  __shared__ int s_pos[256];    // position in the tile's list
-  __shared__ __align__(4) uint8_t s_idx[4][256];  // per wave: staged slots reaching its row
-  __shared__ int s_wcnt[5][4];
-  __shared__ unsigned long long s_nb;
-  const int tile = (int)(blockIdx.x >> 2), quarter = (int)(blockIdx.x & 3);
-  const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, e = lane >> 4;
-  const int px = (tile % k.ntx) * kTile + col;
-  const int py = (tile / k.ntx) * kTile + 4 * quarter + (tid >> 6);
-  const bool inside = px < k.width && py < k.height;
-  const TileBox box = tile_box(k, tile);
-  const uint32_t start = tile_ranges[2 * tile], end = tile_ranges[2 * tile + 1];
-  const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
-  bool done = !inside;
-  float thr = k.t_min;  // stop threshold on the next transmittance (see render_fwd_kernel)
-  if (!kHalf && fb_stop && F && inside) {
-    const float vis = 1.0f - F[(int64_t)py * k.width + px].w;
-    thr = vis > 0.0f ? k.t_min / vis : __builtin_huge_valf();
-    done = vis < k.t_min;
-  }
-  float amin_l = done ? __builtin_huge_valf() : k.alpha_min;
-  float T = 1.0f;      // the pixel's chain through the steps so far (same in its four lanes)
-  float Tlast = 1.0f;  // the chain after this lane's last entry that passed the threshold
-  float cr = 0.0f, cg = 0.0f, cb = 0.0f;
-  uint32_t lastk = 0, nb = 0;
-  const bool odd = lane & 16, high = lane & 32;
-  if (tid == 0) s_nb = 0;
-  const uint32_t lastpos = end > start ? end - 1 : start;
-  Rec rec{};
-  uint32_t gid_next = 0;
-  if (end > start) {  // uniform
-    const uint32_t gid0 = values[min(start + tid, lastpos)];
-    gid_next = values[min(start + 256 + tid, lastpos)];
-    rec = gather_rec(gid0, start + tid < end, means2d, conic_opacity, rgb);
-  }
-  for (uint32_t b0 = start; b0 < end; b0 += 256) {
-    if (__syncthreads_count(done) == 256) break;
-    const float3 cn = conic_of(rec.co);
-    const uint32_t rows = rec.valid ? splat_rows_single(rec.m.x, rec.m.y, cn.x, cn.y, cn.z,
-                                                        rec.co.w, k.alpha_min, box, 4 * quarter)
-                                    : 0u;
-    const bool keep = rows != 0u;
-    int pos, wcnt;
-    compact_rows(keep, rows, s_wcnt, s_idx, pos, wcnt);
-    if (keep) {
-      const Splat sp = make_splat(rec.m, rec.co);
-      s_ga[pos] = make_float4(sp.u, sp.v, sp.qa, sp.qb);
-      s_gb[pos] = make_float4(sp.qc, sp.lo, rec.r, rec.g);
-      s_bl[pos] = rec.b;
-      s_pos[pos] = (int)(b0 - start) + tid;
-    }
-    __syncthreads();
-    const uint32_t nxt = b0 + 256 + tid;
-    const uint32_t gid_after = values[min(b0 + 512 + tid, lastpos)];
-    rec = gather_rec(gid_next, nxt < end, means2d, conic_opacity, rgb);
-    gid_next = gid_after;
-    if (__ballot(!done)) {
-      // lanes past the end of the wave's list read the step's first entry
-      // (every value read is finite) and blend nothing
-      const uint8_t* my_idx = s_idx[tid >> 6];
-      int jl = -1;  // position in the wave's list of the lane's last blended entry
-      for (int j0 = 0; j0 < wcnt; j0 += 4) {
-        const int jw = j0 + e;
-        const int j = my_idx[jw < wcnt ? jw : j0];
-        const float4 ga = s_ga[j], gb = s_gb[j];
-        const float bl = s_bl[j];
-        const float al = splat_alpha(fx - ga.x, fy - ga.y, ga.z, ga.w, gb.x, gb.y, k.alpha_max);
-        // 0 where the lane blends nothing: past the list, below alpha_min, or
-        // the pixel has stopped
-        const float a = (jw < wcnt && al >= amin_l) ? al : 0.0f;
-        const float om = 1.0f - a;
-        const Swapped p1 = swap_bit4(om);
-        const float t1 = p1.first * p1.second;
-        const Swapped p2 = swap_bit5(t1);
-        const float in1 = odd ? t1 : om, ex1 = odd ? p1.first : 1.0f;
-        const float Tn = T * (high ? in1 * p2.first : in1);  // after the entry
-        const float Tc = T * (high ? ex1 * p2.first : ex1);  // before it
-        const bool ok = Tn >= thr;
-        // a zero weight adds exactly zero (colours are finite and >= 0)
-        const float wgt = ok ? a * Tc : 0.0f;
-        cr = fmaf(gb.z, wgt, cr);
-        cg = fmaf(gb.w, wgt, cg);
-        cb = fmaf(bl, wgt, cb);
-        const bool blend = ok && a != 0.0f;
-        jl = blend ? jw : jl;
-        nb += blend ? 1u : 0u;
-        Tlast = ok ? Tn : Tlast;
-        T *= p2.first * p2.second;  // through the step's four entries
-        done = done || T < thr;
-        amin_l = done ? __builtin_huge_valf() : amin_l;
-        if (!__ballot(!done)) break;  // wave-uniform
-      }
-      if (jl >= 0) lastk = (uint32_t)s_pos[my_idx[jl]] + 1;
-    }
-    // s_wcnt is rewritten only after the next barrier
-  }
-  // combine the pixel's four lanes
-  {
-    const Swapped r1 = swap_bit4(cr), g1 = swap_bit4(cg), c1 = swap_bit4(cb), t1 = swap_bit4(Tlast);
-    const Swapped r2 = swap_bit5(r1.first + r1.second), g2 = swap_bit5(g1.first + g1.second),
-                  c2 = swap_bit5(c1.first + c1.second), t2 = swap_bit5(fminf(t1.first, t1.second));
-    cr = r2.first + r2.second;
-    cg = g2.first + g2.second;
-    cb = c2.first + c2.second;
-    T = fminf(t2.first, t2.second);
-    const Swapped k1 = swap_bit4(__uint_as_float(lastk));
-    const uint32_t l1 = max(__float_as_uint(k1.first), __float_as_uint(k1.second));
-    const Swapped k2 = swap_bit5(__uint_as_float(l1));
-    lastk = max(__float_as_uint(k2.first), __float_as_uint(k2.second));
-  }
-  if (kHalf && rect) {
-    // coverage of the cached image: tiles holding any pixel that blended
-    if (__syncthreads_or(inside && T < 1.0f) && tid == 0) {
-      const int tx = tile % k.ntx, ty = tile / k.ntx;
-      atomicMin(&rect[0], tx * kTile);
-      atomicMin(&rect[1], ty * kTile);
-      atomicMax(&rect[2], min(tx * kTile + kTile, k.width));
-      atomicMax(&rect[3], min(ty * kTile + kTile, k.height));
-    }
-  }
-  if (inside && e == 0) {
-    const int64_t p = (int64_t)py * k.width + px;
-    if (kHalf) {
-      const _Float16 h[4] = {(_Float16)cr, (_Float16)cg, (_Float16)cb, (_Float16)(1.0f - T)};
-      out16[p] = __builtin_bit_cast(uint2, h);
-    } else {
-      const float4 f = F ? F[p] : make_float4(0, 0, 0, 0);
-      const float4 bb = B ? B[p] : make_float4(0, 0, 0, 0);
-      const float s = 1.0f - f.w;
-      out[p] = make_float4(f.x + s * (cr + T * bb.x), f.y + s * (cg + T * bb.y),
-                           f.z + s * (cb + T * bb.z), f.w + s * (1.0f - T * (1.0f - bb.w)));
-      final_T[p] = T;
-      last[p] = lastk;
-    }
-  }
-  if (n_blends) {
-    const unsigned long long wsum = wave_sum_u32(nb);
-    __syncthreads();
-    if (lane == 0) atomicAdd(&s_nb, wsum);
-    __syncthreads();
-    if (tid == 0 && s_nb) atomicAdd(n_blends, s_nb);
-  }
+// Before a forward that splits: no slot taken; in frames that may take the rows
+// layout, no walk of any tile yet.
+__global__ __launch_bounds__(256) void split_clear_kernel(SplitLayout sp, int tiles) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < 16) sp.hdr[i] = 0u;
+  if (i < tiles) sp.work[i] = sp.walk[i] = 0u;
 }
 
 __global__ void rect_init_kernel(int* __restrict__ rect, int width, int height) {
@@ -491,13 +540,24 @@ int32_t launch_render_fwd(const abcd_camera& cam, const abcd_raster_params& prm,
     ABCD_HIP(hipGetLastError());
     return ABCD_OK;
   }
-  if (split.ckpt) TRY_STATUS(launch_zero(reinterpret_cast<float*>(split.hdr), 16, stream));
-  ABCD_LAUNCH("render_fwd", render_fwd_kernel<false>, grid, kBlock, 0, stream, k, tile_ranges,
-              values_sorted, reinterpret_cast<const float2*>(means2d),
-              reinterpret_cast<const float4*>(conic_opacity), rgb,
-              reinterpret_cast<const float4*>(F), reinterpret_cast<const float4*>(B),
-              reinterpret_cast<float4*>(out_rgba), final_T, last, n_blends, tile_order, nullptr,
-              nullptr, (int)(prm.flags & ABCD_FLAG_FB_STOP), split);
+  const int few = k.ntiles <= kFewTiles ? grid : 0;
+  if (split.ckpt) {
+    const int tiles = few ? k.ntiles : 0;
+    ABCD_LAUNCH("zero_fill", split_clear_kernel, std::max(1, (tiles + 255) / 256), 256, 0, stream,
+                split, tiles);
+  }
+#define ABCD_FWD(kFew, blocks)                                                                    \
+  ABCD_LAUNCH("render_fwd", (render_fwd_kernel<false, kFew>), blocks, kBlock, 0, stream, k,       \
+              tile_ranges, values_sorted, reinterpret_cast<const float2*>(means2d),               \
+              reinterpret_cast<const float4*>(conic_opacity), rgb,                                \
+              reinterpret_cast<const float4*>(F), reinterpret_cast<const float4*>(B),             \
+              reinterpret_cast<float4*>(out_rgba), final_T, last, n_blends, tile_order, nullptr,  \
+              nullptr, (int)(prm.flags & ABCD_FLAG_FB_STOP), split, few)
+  if (few)
+    ABCD_FWD(true, std::max(grid, 4 * k.ntiles));
+  else
+    ABCD_FWD(false, grid);
+#undef ABCD_FWD
   ABCD_HIP(hipGetLastError());
   return ABCD_OK;
 }
@@ -521,11 +581,18 @@ int32_t launch_render_cache(const abcd_camera& cam, const abcd_raster_params& pr
     ABCD_HIP(hipGetLastError());
     return ABCD_OK;
   }
-  ABCD_LAUNCH("render_cache", render_fwd_kernel<true>, grid, kBlock, 0, stream, k, tile_ranges,
-              values_sorted, reinterpret_cast<const float2*>(means2d),
-              reinterpret_cast<const float4*>(conic_opacity), rgb, nullptr, nullptr, nullptr,
-              nullptr, nullptr, nullptr, tile_order, reinterpret_cast<uint2*>(image_f16), rect, 0,
-              SplitLayout{});
+  const int few = k.ntiles <= kFewTiles ? grid : 0;
+#define ABCD_CACHE(kFew, blocks)                                                                  \
+  ABCD_LAUNCH("render_cache", (render_fwd_kernel<true, kFew>), blocks, kBlock, 0, stream, k,      \
+              tile_ranges, values_sorted, reinterpret_cast<const float2*>(means2d),               \
+              reinterpret_cast<const float4*>(conic_opacity), rgb, nullptr, nullptr, nullptr,     \
+              nullptr, nullptr, nullptr, tile_order, reinterpret_cast<uint2*>(image_f16), rect,   \
+              0, SplitLayout{}, few)
+  if (few)
+    ABCD_CACHE(true, std::max(grid, 4 * k.ntiles));
+  else
+    ABCD_CACHE(false, grid);
+#undef ABCD_CACHE
   ABCD_HIP(hipGetLastError());
   return ABCD_OK;
 }

@@ -150,3 +150,46 @@ def test_binning_without_capacity_counts(api, n):
     assert full["n_isect"] == int(proj["tiles_touched"].sum())
     assert int(got["tile_ranges"].abs().max()) == 0
     assert torch.equal(got["tile_order"].cpu(), torch.arange(len(got["tile_order"]), dtype=torch.int32))
+
+
+@pytest.mark.parametrize("size", [(272, 256), (505, 499)])
+@pytest.mark.parametrize("n", [1500, 40_000])
+def test_layout_by_pairs(api, n, size):
+    """Frames of 272 and 1,024 tiles with lists that hold fewer and more pairs than
+    the rows layout is chosen for, unsplit, split and as a cached render: parity
+    bars against the oracle, and the split and unsplit forwards bit-identical."""
+    from paper_2608_27735_amd.camera import RasterParams, look_at
+    r = S.rng(700 + n)
+    cam = look_at((0.1, -3.0, 0.8), (0, 0, 0), *size)
+    prm = RasterParams(sh_degree=0)
+    sc = S.gaussians(r, r.uniform(-0.6, 0.6, (n, 3)), 0, np.log(0.02), 0.4)
+    F, B = S.background_pair(r, cam.height, cam.width)
+    ref = O.step(cam, prm, sc, F=F, B=B, rel_margin=1e-4)
+    m = len(ref["sorted_values"])
+    say("layout by pairs", n, size, m)
+    assert (m <= 65536) == (n == 1500)
+    knife = ref["fwd"]["knife"]
+    dL = np.where(knife[..., None], 0, S.upstream_grad(r, cam.height, cam.width)).astype(np.float32)
+    ref = O.step(cam, prm, sc, F=F, B=B, dL_dout=dL.astype(np.float64), rel_margin=1e-4)
+    d = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to(dev())
+    params = {k: d(v) for k, v in sc.items()}
+    proj = api.project(cam, prm, **params)
+    bins = api.bin_sort(cam.width, cam.height, proj)
+    split = api.make_split(m // 256 + api.n_tiles(*size) + 1, 256)
+    outs = []
+    for sp in (None, split):
+        fwd = api.render_fwd(cam, prm, bins, proj, F=d(F), B=d(B), split=sp)
+        grads = api.render_bwd(cam, prm, params, proj, bins, fwd, d(dL), F=d(F), B=d(B), split=sp)
+        torch.cuda.synchronize()
+        outs.append(fwd)
+        err = np.abs(fwd["out"].cpu().numpy() - ref["fwd"]["out"])[~knife]
+        assert err.max() <= 1e-5
+        assert np.array_equal(fwd["last"].cpu().numpy().view(np.uint32)[~knife],
+                              ref["fwd"]["last"][~knife])
+        for k in params:
+            g, gr = grads[k].cpu().numpy().astype(np.float64), ref["grads"][k]
+            assert np.linalg.norm(g - gr) <= 1e-4 * max(np.linalg.norm(gr), 1e-30), (k, sp is None)
+    for k in ("out", "final_T", "last"):
+        assert torch.equal(outs[0][k], outs[1][k])
+    plain = api.render_fwd(cam, prm, bins, proj)["out"]
+    assert torch.equal(api.render_cache(cam, prm, bins, proj), plain.half())
