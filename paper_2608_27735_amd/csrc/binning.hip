@@ -37,6 +37,8 @@
 //                          last: tile_ranges
 //   l2_scatter             values (and keys), tile-major, depth order; its
 //                          first workgroup: the forward's tile order
+#include <atomic>
+
 #include <algorithm>
 
 #include "schedule.h"
@@ -1195,18 +1197,21 @@ __global__ __launch_bounds__(kBlock) void l2_scatter_kernel(
 //
 // A small active block (the regime where ABCD's partitions hold few Gaussians
 // and launch costs dominate) is binned in two launches instead of the general
-// path's 22: one workgroup sorts the Gaussians by depth in LDS, counts each
+// path's nine: one workgroup sorts the Gaussians by depth in LDS, counts each
 // tile's list from the rectangles and scans the counts into the tile ranges;
 // then one workgroup per tile collects, in depth order, the Gaussians whose
 // rectangle covers it. The lists are the same as the general path's.
 
-constexpr int kSmallN = 2048;        // Gaussians the one-workgroup sort holds
+constexpr int kSmallN = 8192;        // Gaussians the one-workgroup sort holds
 constexpr int kSmallTiles = 2048;    // tiles of the frame (each coordinate below 256)
 constexpr int kSmallThreads = 1024;
+// (ntx + 1)(nty + 1) with ntx nty <= kSmallTiles and both at most 256
+constexpr int kSmallDiff = kSmallTiles + 256 + kSmallTiles / 256 + 1;
 constexpr int kSmallWaves = kSmallThreads / 64;
-constexpr int kSmallKeyBytes = kSmallN * 4;
-static_assert(kSmallThreads == kOrderThreads, "the small path orders tiles with order_tiles");
 
+// The general path's nine launches take 75 us however few Gaussians there are
+// (launches of 2,049 to 8,192 Gaussians at 128x128 and 720x640: 66 to 114 us
+// against 26 to 64 here, whatever the Gaussians' sizes).
 bool small_path(int64_t n, const Geo& g) {
   return n <= kSmallN && (int64_t)g.ntx * g.nty <= kSmallTiles && g.ntx <= 256 && g.nty <= 256;
 }
@@ -1242,103 +1247,177 @@ __device__ __forceinline__ uint32_t scan_small(uint32_t v, uint32_t* s, uint32_t
   return before + incl - v;
 }
 
-// One workgroup: keys (fp32 depth bits; Gaussians with no tile last) and byte
-// rectangles; a stable LSD radix sort by key in LDS (8-bit digits; wave w
-// ranks its 128 consecutive entries with ballots, the waves' digit counts give
-// the offsets), which keeps equal keys in index order; per-tile counts by LDS
-// atomics over each rectangle; their exclusive scan (tile_off, tile_ranges);
+// Inclusive prefix sum over the wave.
+__device__ __forceinline__ int wave_prefix_i32(int v) {
+  const int lane = __lane_id();
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int y = __shfl_up(v, d, 64);
+    if (lane >= d) v += y;
+  }
+  return v;
+}
+
+// Workgroup memory of the one-workgroup sort of up to 1,024 kItems Gaussians.
+template <int kItems>
+struct SmallLds {
+  uint32_t key[2][kSmallThreads * kItems];
+  uint32_t rect[kSmallThreads * kItems];
+  uint16_t val[2][kSmallThreads * kItems];
+  uint16_t cnt[kSmallWaves][256];
+  uint32_t tcount[kSmallTiles];
+  // (ntx + 1) x (nty + 1) differences, where the second key buffer is too small
+  // to hold them until the sort needs it
+  int own_diff[kItems >= 4 ? 1 : kSmallDiff];
+  uint32_t scan[kSmallWaves];
+  unsigned long long m;
+  uint32_t lo, hi;
+};
+
+// One workgroup: keys (fp32 depth bits less the smallest; Gaussians with no
+// tile last) and byte rectangles; a stable LSD radix sort by key in LDS (8-bit
+// digits, as many as the keys' range has; wave w ranks its 64 kItems
+// consecutive entries with ballots, the waves' digit counts give the
+// offsets), which keeps equal keys in index order; per-tile counts from a 2D
+// difference array (four LDS atomics a rectangle: an atomic per covered tile
+// took 340 us for 8,192 Gaussians over 66 tiles each); their exclusive scan (tile_off, tile_ranges);
 // the sorted Gaussians and their rectangles for the per-tile collection; M
 // and the overflow decision in the header (on overflow
 // every range is empty), and the forward's tile order.
+template <int kItems>
 __global__ __launch_bounds__(kSmallThreads) void bin_small_sort_kernel(
     int n, const float* __restrict__ depth, const uint32_t* __restrict__ tiles,
     const float* __restrict__ means2d, const float* __restrict__ extent, Geo geo,
     unsigned long long capacity, uint32_t* __restrict__ sorted_g, uint32_t* __restrict__ sorted_rect,
     uint32_t* __restrict__ tile_off, uint32_t* __restrict__ tile_ranges,
     uint32_t* __restrict__ tile_order, WsHeader* __restrict__ hdr) {
-  __shared__ uint32_t s_key[2][kSmallN];
-  __shared__ uint16_t s_val[2][kSmallN];
-  __shared__ uint32_t s_rect[kSmallN];
-  __shared__ uint16_t s_cnt[kSmallWaves][256];
-  __shared__ uint32_t s_tcount[kSmallTiles];
-  __shared__ uint32_t s_scan[kSmallWaves];
-  __shared__ unsigned long long s_m;
-  __shared__ uint32_t s_kor, s_kand;
+  extern __shared__ __align__(16) unsigned char small_lds[];
+  SmallLds<kItems>& s = *reinterpret_cast<SmallLds<kItems>*>(small_lds);
+  constexpr int kPerWave = 64 * kItems;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int ntiles = geo.ntx * geo.nty;
-  for (int t = tid; t < ntiles; t += kSmallThreads) s_tcount[t] = 0;
+  // every load of the thread in flight at once
+  uint32_t tt[kItems];
+  float dp[kItems];
+  float2 mm[kItems], ee[kItems];
+#pragma unroll
+  for (int it = 0; it < kItems; ++it) {
+    const int i = min(it * kSmallThreads + tid, n - 1);
+    tt[it] = tiles[i];
+    dp[it] = depth[i];
+    mm[it] = reinterpret_cast<const float2*>(means2d)[i];
+    ee[it] = reinterpret_cast<const float2*>(extent)[i];
+  }
+  static_assert(kItems < 4 || sizeof(s.key[1]) >= kSmallDiff * sizeof(int), "differences");
+  int* const diff = kItems >= 4 ? reinterpret_cast<int*>(s.key[1]) : s.own_diff;
+  const int dw = geo.ntx + 1;
+  for (int t = tid; t < dw * (geo.nty + 1); t += kSmallThreads) diff[t] = 0;
   if (tid == 0) {
-    s_m = 0;
-    s_kor = 0u;
-    s_kand = 0xffffffffu;
+    s.m = 0;
+    s.lo = 0xffffffffu;
+    s.hi = 0u;
   }
   __syncthreads();
   unsigned long long m = 0;
-  uint32_t kor = 0u, kand = 0xffffffffu;  // bits set in some key / in every key
-  for (int i = tid; i < n; i += kSmallThreads) {
-    const uint32_t tt = tiles[i];
-    uint32_t key = 0xffffffffu;
-    int x0 = 1, y0 = 0, x1 = 0, y1 = 0;
-    if (tt != 0) {
-      key = __float_as_uint(depth[i]);
-      const float2 mm = reinterpret_cast<const float2*>(means2d)[i];
-      const float2 ex = reinterpret_cast<const float2*>(extent)[i];
-      if (!tile_rect(mm.x, mm.y, ex.x, ex.y, geo.ntx, geo.nty, x0, y0, x1, y1))
-        x0 = 1, y0 = 0, x1 = 0, y1 = 0;
-    }
-    s_key[0][i] = key;
-    s_val[0][i] = (uint16_t)i;
-    s_rect[i] = pack_rect8(x0, y0, x1, y1);
-    kor |= key;
-    kand &= key;
-    if (x1 >= x0) {
-      m += tt;
-      for (int y = y0; y <= y1; ++y)
-        for (int x = x0; x <= x1; ++x) atomicAdd(&s_tcount[y * geo.ntx + x], 1u);
+  uint32_t lo = 0xffffffffu, hi = 0u;  // range of the keys of Gaussians with a tile
+#pragma unroll
+  for (int it = 0; it < kItems; ++it) {
+    const int i = it * kSmallThreads + tid;
+    if (i < n) {
+      int x0 = 1, y0 = 0, x1 = 0, y1 = 0;
+      if (tt[it] != 0) {
+        lo = min(lo, __float_as_uint(dp[it]));
+        hi = max(hi, __float_as_uint(dp[it]));
+        if (!tile_rect(mm[it].x, mm[it].y, ee[it].x, ee[it].y, geo.ntx, geo.nty, x0, y0, x1, y1))
+          x0 = 1, y0 = 0, x1 = 0, y1 = 0;
+      }
+      s.val[0][i] = (uint16_t)i;
+      s.rect[i] = pack_rect8(x0, y0, x1, y1);
+      if (x1 >= x0) {
+        m += tt[it];
+        atomicAdd(&diff[y0 * dw + x0], 1);
+        atomicSub(&diff[y0 * dw + x1 + 1], 1);
+        atomicSub(&diff[(y1 + 1) * dw + x0], 1);
+        atomicAdd(&diff[(y1 + 1) * dw + x1 + 1], 1);
+      }
     }
   }
   const unsigned long long wm = wave_sum_u64(m);
-  if (lane == 0 && wm) atomicAdd(&s_m, wm);
+  if (lane == 0 && wm) atomicAdd(&s.m, wm);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
-    kor |= (uint32_t)__shfl_xor((int)kor, off, 64);
-    kand &= (uint32_t)__shfl_xor((int)kand, off, 64);
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, off, 64));
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, off, 64));
   }
   if (lane == 0) {
-    atomicOr(&s_kor, kor);
-    atomicAnd(&s_kand, kand);
+    atomicMin(&s.lo, lo);
+    atomicMax(&s.hi, hi);
   }
   __syncthreads();
-  const unsigned long long mt = s_m;
+  // prefix sums of the differences along the rows, a wave a row, then along the
+  // columns, a wave a column, into the tile counts
+  for (int y = w; y < geo.nty; y += kSmallWaves) {
+    int carry = 0;
+    for (int x0 = 0; x0 < geo.ntx; x0 += 64) {
+      const int x = x0 + lane;
+      const int v = wave_prefix_i32(x < geo.ntx ? diff[y * dw + x] : 0) + carry;
+      if (x < geo.ntx) diff[y * dw + x] = v;
+      carry = __builtin_amdgcn_readlane(v, 63);
+    }
+  }
+  __syncthreads();
+  for (int x = w; x < geo.ntx; x += kSmallWaves) {
+    int carry = 0;
+    for (int y0 = 0; y0 < geo.nty; y0 += 64) {
+      const int y = y0 + lane;
+      const int v = wave_prefix_i32(y < geo.nty ? diff[y * dw + x] : 0) + carry;
+      if (y < geo.nty) s.tcount[y * geo.ntx + x] = (uint32_t)v;
+      carry = __builtin_amdgcn_readlane(v, 63);
+    }
+  }
+  const unsigned long long mt = s.m;
   const bool over = mt > capacity || mt >= (1ull << 32);
-  // radix sort: wave w owns positions [128 w, 128 w + 128); the waves past
-  // the last key (nw and on) hold nothing, and a digit that every key shares
-  // would leave the order as it is, so its pass is skipped
+  lo = s.lo;
+  hi = s.hi;
+  // as in depth_keys: no visible Gaussian, or a depth that is not positive
+  if (lo > hi) lo = hi = 0u;
+  if (hi >= 0x80000000u) lo = 0u, hi = 0xfffffffeu;
+  const uint32_t none = hi - lo + 1u;
+#pragma unroll
+  for (int it = 0; it < kItems; ++it) {
+    const int i = it * kSmallThreads + tid;
+    if (i < n) s.key[0][i] = tt[it] != 0 ? __float_as_uint(dp[it]) - lo : none;
+  }
+  // radix sort: wave w owns positions [kPerWave w, kPerWave (w + 1)); the waves
+  // past the last key (nw and on) hold nothing
   const uint64_t lt = lanemask_lt();
-  const int nw = (n + 127) / 128;
-  const uint32_t varying = s_kor ^ s_kand;
+  const int nw = (n + kPerWave - 1) / kPerWave;
+  const int passes = (32 - __clz(none) + 7) / 8;
   int src = 0;  // buffer holding the order so far (uniform)
 #pragma unroll 1
-  for (int pass = 0; pass < 4; ++pass) {
+  for (int pass = 0; pass < passes; ++pass) {
     const int shift = 8 * pass;
-    if (((varying >> shift) & 255u) == 0u) continue;  // uniform
-    for (int i = tid; i < nw * 256; i += kSmallThreads) (&s_cnt[0][0])[i] = 0;
+    for (int i = tid; i < nw * 256; i += kSmallThreads) (&s.cnt[0][0])[i] = 0;
     __syncthreads();
-    uint32_t key[2], rank[2];
-    uint16_t val[2];
+    uint32_t key[kItems], rank[kItems];
+    uint16_t val[kItems];
 #pragma unroll
-    for (int it = 0; it < 2; ++it) {
-      const int idx = 128 * w + 64 * it + lane;
+    for (int it = 0; it < kItems; ++it) {
+      const int idx = kPerWave * w + 64 * it + lane;
       const bool valid = idx < n;
-      key[it] = valid ? s_key[src][idx] : 0u;
-      val[it] = valid ? s_val[src][idx] : (uint16_t)0;
+      key[it] = valid ? s.key[src][idx] : 0u;
+      val[it] = valid ? s.val[src][idx] : (uint16_t)0;
+    }
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) {
+      const bool valid = kPerWave * w + 64 * it + lane < n;
       const uint32_t d = (key[it] >> shift) & 255u;
       const uint64_t peers = match_digit(d, __ballot(valid));
       rank[it] = 0;
       if (valid) {
-        rank[it] = s_cnt[w][d] + (uint32_t)__popcll(peers & lt);
+        rank[it] = s.cnt[w][d] + (uint32_t)__popcll(peers & lt);
         if (lane == __ffsll((unsigned long long)peers) - 1)
-          s_cnt[w][d] = (uint16_t)(s_cnt[w][d] + __popcll(peers));
+          s.cnt[w][d] = (uint16_t)(s.cnt[w][d] + __popcll(peers));
       }
     }
     __syncthreads();
@@ -1346,54 +1425,53 @@ __global__ __launch_bounds__(kSmallThreads) void bin_small_sort_kernel(
     // waves' offsets in place
     uint32_t tot_d = 0;
     if (tid < 256)
-      for (int v = 0; v < nw; ++v) tot_d += s_cnt[v][tid];
+      for (int v = 0; v < nw; ++v) tot_d += s.cnt[v][tid];
     uint32_t total;
-    uint32_t base = scan_small(tid < 256 ? tot_d : 0u, s_scan, &total);
+    uint32_t base = scan_small(tid < 256 ? tot_d : 0u, s.scan, &total);
     if (tid < 256)
       for (int v = 0; v < nw; ++v) {
-        const uint32_t c = s_cnt[v][tid];
-        s_cnt[v][tid] = (uint16_t)base;
+        const uint32_t c = s.cnt[v][tid];
+        s.cnt[v][tid] = (uint16_t)base;
         base += c;
       }
     __syncthreads();
 #pragma unroll
-    for (int it = 0; it < 2; ++it) {
-      const int idx = 128 * w + 64 * it + lane;
-      if (idx < n) {
-        const uint32_t pos = s_cnt[w][(key[it] >> shift) & 255u] + rank[it];
-        s_key[src ^ 1][pos] = key[it];
-        s_val[src ^ 1][pos] = val[it];
+    for (int it = 0; it < kItems; ++it) {
+      if (kPerWave * w + 64 * it + lane < n) {
+        const uint32_t pos = s.cnt[w][(key[it] >> shift) & 255u] + rank[it];
+        s.key[src ^ 1][pos] = key[it];
+        s.val[src ^ 1][pos] = val[it];
       }
     }
     __syncthreads();
     src ^= 1;
   }
   for (int j = tid; j < n; j += kSmallThreads) {
-    const uint32_t g = s_val[src][j];
+    const uint32_t g = s.val[src][j];
     sorted_g[j] = g;
-    sorted_rect[j] = s_rect[g];
+    sorted_rect[j] = s.rect[g];
   }
   // tile ranges: runs of `per` tiles per thread
   const int per = (ntiles + kSmallThreads - 1) / kSmallThreads;
-  const int lo = min(ntiles, per * tid), hi = min(ntiles, lo + per);
+  const int t_lo = min(ntiles, per * tid), t_hi = min(ntiles, t_lo + per);
   uint32_t sum = 0;
-  for (int t = lo; t < hi; ++t) sum += over ? 0u : s_tcount[t];
+  for (int t = t_lo; t < t_hi; ++t) sum += over ? 0u : s.tcount[t];
   uint32_t total;
-  uint32_t run = scan_small(sum, s_scan, &total);
-  for (int t = lo; t < hi; ++t) {
-    const uint32_t c = over ? 0u : s_tcount[t];
+  uint32_t run = scan_small(sum, s.scan, &total);
+  for (int t = t_lo; t < t_hi; ++t) {
+    const uint32_t c = over ? 0u : s.tcount[t];
     tile_off[t] = run;
     tile_ranges[2 * t] = run;
     tile_ranges[2 * t + 1] = run + c;
     run += c;
-    if (over) s_tcount[t] = 0u;
+    if (over) s.tcount[t] = 0u;
   }
   if (tile_order) {
     // the forward's schedule: heaviest lists first (identity on overflow); the
     // bucket keys go where the sort's second key buffer was
-    static_assert(kSmallKeyBytes >= kSmallTiles, "bucket keys fit the spare key buffer");
+    static_assert(sizeof(s.key[1]) >= kSmallTiles, "bucket keys fit the spare key buffer");
     __syncthreads();
-    order_tiles(ntiles, s_tcount, tile_order, reinterpret_cast<uint8_t*>(s_key[1]));
+    order_tiles(ntiles, s.tcount, tile_order, reinterpret_cast<uint8_t*>(s.key[1]));
   }
   if (tid == 0) {
     hdr->m = mt;
@@ -1404,7 +1482,9 @@ __global__ __launch_bounds__(kSmallThreads) void bin_small_sort_kernel(
 }
 
 // One workgroup per tile: the sorted Gaussians whose rectangle covers the
-// tile, in sorted order, 256 positions per round (ballots rank them).
+// tile, in sorted order. Wave w takes a quarter of the positions, counts its
+// hits, and stores them once the counts of the waves before it are known: the
+// rectangles are read twice (from cache), 8 x 64 at a time, with one barrier.
 __global__ __launch_bounds__(256) void bin_small_collect_kernel(
     int n, const float* __restrict__ depth, Geo geo, const uint32_t* __restrict__ sorted_g,
     const uint32_t* __restrict__ sorted_rect, const uint32_t* __restrict__ tile_off,
@@ -1415,34 +1495,51 @@ __global__ __launch_bounds__(256) void bin_small_collect_kernel(
   const int t = blockIdx.x, tx = t % geo.ntx, ty = t / geo.ntx;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const uint64_t lt = lanemask_lt();
-  uint32_t run = tile_off[t];
-  for (int j0 = 0; j0 < n; j0 += 256) {
-    const int j = j0 + threadIdx.x;
-    bool hit = false;
-    uint32_t g = 0;
-    if (j < n) {
-      const uint32_t r = sorted_rect[j];
-      const int x0 = r & 255, x1 = (r >> 8) & 255, y0 = (r >> 16) & 255, y1 = r >> 24;
-      hit = x0 <= tx && tx <= x1 && y0 <= ty && ty <= y1;
-      g = sorted_g[j];
-    }
-    const uint64_t bal = __ballot(hit);
-    if (lane == 0) s_w[w] = (uint32_t)__popcll(bal);
-    __syncthreads();
-    uint32_t before = 0, tot = 0;
+  const int quarter = ((n + 255) / 256) * 64;  // positions per wave
+  const int j0 = w * quarter, j1 = min(n, j0 + quarter);
+  const uint32_t off = tile_off[t];
+  auto covers = [&](uint32_t r) {
+    const int x0 = r & 255, x1 = (r >> 8) & 255, y0 = (r >> 16) & 255, y1 = r >> 24;
+    return x0 <= tx && tx <= x1 && y0 <= ty && ty <= y1;
+  };
+  constexpr int kAhead = 8;
+  constexpr uint32_t kEmpty = 1u;  // x0 = 1 > x1 = 0
+  uint32_t count = 0;
+  for (int j = j0; j < j1; j += 64 * kAhead) {
+    uint32_t r[kAhead];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const uint32_t c = s_w[v];
-      before += v < w ? c : 0u;
-      tot += c;
+    for (int a = 0; a < kAhead; ++a) {
+      const int i = j + 64 * a + lane;
+      r[a] = i < j1 ? sorted_rect[i] : kEmpty;
     }
-    if (hit) {
-      const uint32_t pos = run + before + (uint32_t)__popcll(bal & lt);
-      values_sorted[pos] = g;
-      if (keys_sorted) keys_sorted[pos] = ((unsigned long long)t << 32) | __float_as_uint(depth[g]);
+#pragma unroll
+    for (int a = 0; a < kAhead; ++a) count += (uint32_t)__popcll(__ballot(covers(r[a])));
+  }
+  if (lane == 0) s_w[w] = count;
+  __syncthreads();
+  uint32_t run = off;
+#pragma unroll
+  for (int v = 0; v < 3; ++v) run += v < w ? s_w[v] : 0u;
+  for (int j = j0; j < j1; j += 64 * kAhead) {
+    uint32_t r[kAhead], g[kAhead];
+#pragma unroll
+    for (int a = 0; a < kAhead; ++a) {
+      const int i = j + 64 * a + lane;
+      r[a] = i < j1 ? sorted_rect[i] : kEmpty;
+      g[a] = i < j1 ? sorted_g[i] : 0u;
     }
-    run += tot;
-    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < kAhead; ++a) {
+      const bool hit = covers(r[a]);
+      const uint64_t bal = __ballot(hit);
+      if (hit) {
+        const uint32_t pos = run + (uint32_t)__popcll(bal & lt);
+        values_sorted[pos] = g[a];
+        if (keys_sorted)
+          keys_sorted[pos] = ((unsigned long long)t << 32) | __float_as_uint(depth[g[a]]);
+      }
+      run += (uint32_t)__popcll(bal);
+    }
   }
 }
 
@@ -1526,9 +1623,27 @@ int32_t launch_bin_sort(int width, int height, int64_t n, const float* means2d, 
   auto u32 = [&](size_t off) { return reinterpret_cast<uint32_t*>(ws + off); };
   if (small_path(n, geo)) {
     const unsigned long long cap_s = (unsigned long long)std::max<int64_t>(capacity, 0);
-    ABCD_LAUNCH("bin_small_sort", bin_small_sort_kernel, 1, kSmallThreads, 0, stream, (int)n,
-                depth, tiles_touched, means2d, extent, geo, cap_s, u32(L.keys_a), u32(L.keys_b),
-                u32(L.tile_off), tile_ranges, tile_order, hdr);
+#define ABCD_SMALL(kItems)                                                                       \
+  do {                                                                                            \
+    static std::atomic<bool> lds_set{false};                                                      \
+    if (!lds_set.load(std::memory_order_acquire)) {                                               \
+      TRY_STATUS(set_max_lds((const void*)bin_small_sort_kernel<kItems>, sizeof(SmallLds<kItems>))); \
+      lds_set.store(true, std::memory_order_release);                                             \
+    }                                                                                             \
+    ABCD_LAUNCH("bin_small_sort", bin_small_sort_kernel<kItems>, 1, kSmallThreads,                \
+                sizeof(SmallLds<kItems>), stream, (int)n, depth, tiles_touched, means2d, extent,  \
+                geo, cap_s, u32(L.keys_a), u32(L.keys_b), u32(L.tile_off), tile_ranges,           \
+                tile_order, hdr);                                                                 \
+  } while (0)
+    if (n <= 1 * kSmallThreads)
+      ABCD_SMALL(1);
+    else if (n <= 2 * kSmallThreads)
+      ABCD_SMALL(2);
+    else if (n <= 4 * kSmallThreads)
+      ABCD_SMALL(4);
+    else
+      ABCD_SMALL(8);
+#undef ABCD_SMALL
     ABCD_LAUNCH("bin_small_collect", bin_small_collect_kernel, ntiles, kBlock, 0, stream, (int)n,
                 depth, geo, u32(L.keys_a), u32(L.keys_b), u32(L.tile_off), hdr, values_sorted,
                 reinterpret_cast<unsigned long long*>(keys_sorted));

@@ -193,3 +193,29 @@ def test_layout_by_pairs(api, n, size):
         assert torch.equal(outs[0][k], outs[1][k])
     plain = api.render_fwd(cam, prm, bins, proj)["out"]
     assert torch.equal(api.render_cache(cam, prm, bins, proj), plain.half())
+
+
+@pytest.mark.parametrize("size", [(203, 117), (4096, 128), (128, 4096), (720, 640)])
+@pytest.mark.parametrize("n", [1, 1024, 1025, 2049, 4097, 8192, 8193])
+def test_binning_small_block_sizes(api, n, size):
+    """Blocks on both sides of each size of the one-workgroup sort (1,024 to 8,192
+    Gaussians) and of the general path, on frames of 104 tiles, of the widest
+    and the highest it takes, and of 1,800, with rectangles from one tile to the
+    whole frame: lists, keys, ranges and M bit-exact against the oracle."""
+    from paper_2608_27735_amd.camera import RasterParams, look_at
+    r = S.rng(800 + n)
+    cam = look_at((0.2, -3.0, 0.9), (0, 0, 0), *size)
+    sc = S.gaussians(r, r.uniform(-1.5, 1.5, (n, 3)), 0, np.log(0.02), 1.2)
+    sc["means"][3::7, 1] -= 4.0  # some behind the camera
+    sc["means"][0] = 0.0  # and one in view
+    prm = RasterParams(sh_degree=0)
+    say("small blocks", n, size)
+    pb = O.project_bin(cam, prm, sc["means"], sc["log_scales"], sc["quats"], sc["opacity_logits"])
+    keys, values, ranges = O.bin(cam.width, cam.height, pb["depth"], pb["rect"], pb["tiles_touched"])
+    proj = api.project(cam, prm, **{k: torch.from_numpy(v).to(dev()) for k, v in sc.items()})
+    b = api.bin_sort(cam.width, cam.height, proj, want_keys=True)
+    m = b["n_isect"]
+    assert m == len(values)
+    assert np.array_equal(b["values"][:m].cpu().numpy().view(np.uint32), values)
+    assert np.array_equal(b["keys"][:m].cpu().numpy().view(np.uint64), keys)
+    assert np.array_equal(b["tile_ranges"].cpu().numpy().view(np.uint32), ranges)
