@@ -6,6 +6,8 @@ fallback: if it is missing, importing the binding raises.
 import ctypes as C
 import os
 
+import numpy as np
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libabcd.so")
 
@@ -107,16 +109,27 @@ def check(status):
     return status
 
 
+def _fill(dst, values):
+    """The first len(dst) numbers of values into a ctypes array. A NumPy array of
+    that size goes as a whole: element by element the three arrays of a camera
+    took 6 of the 13 us that a call of a kernel spends on the host."""
+    if type(values) is np.ndarray and values.size == len(dst):
+        dst[:] = values.ravel().tolist()
+        return
+    for i in range(len(dst)):
+        dst[i] = float(values[i])
+
+
 def camera_struct(cam):
     c = abcd_camera()
     c.width, c.height = int(cam.width), int(cam.height)
     c.fx, c.fy, c.cx, c.cy = float(cam.fx), float(cam.fy), float(cam.cx), float(cam.cy)
-    R = [float(x) for row in cam.R for x in row] if hasattr(cam.R[0], "__len__") else list(cam.R)
-    for i in range(9):
-        c.R[i] = float(R[i])
-    for i in range(3):
-        c.t[i] = float(cam.t[i])
-        c.campos[i] = float(cam.campos[i])
+    R = cam.R
+    if (type(R) is not np.ndarray or R.size != 9) and hasattr(R[0], "__len__"):
+        R = [float(x) for row in R for x in row]
+    _fill(c.R, R)
+    _fill(c.t, cam.t)
+    _fill(c.campos, cam.campos)
     c.near_plane = float(cam.near)
     return c
 

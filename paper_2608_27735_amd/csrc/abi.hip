@@ -1,6 +1,7 @@
 // abi.hip -- the extern "C" entry points declared in include/abcd.h: argument
 // validation on the host (before any HIP call), dispatch to the kernels,
 // error reporting and optional per-kernel event timing.
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -159,6 +160,52 @@ int32_t noalloc_scratch(void** out) {
   return ABCD_OK;
 }
 
+// Pinned words for the intersection count that abcd_bin_sort reads back: a
+// copy to pageable memory goes through a staging buffer of the runtime's and
+// left the host 9 us behind a plain wait (48 us against 39 us for a binning of
+// 6,144 Gaussians; 42 us with the pinned word). kReadSlots words (512 bytes)
+// are allocated once and kept; each is taken by one call at a time, from any
+// thread. A call that finds none free, or no pinned memory, copies to its own
+// variable. The allocation is made in relaxed capture mode, so that it does
+// not disturb a graph that another thread records.
+constexpr int kReadSlots = 64;
+std::atomic<uint64_t> g_read_taken{0};
+std::once_flag g_read_once;
+unsigned long long* g_read_words = nullptr;
+
+struct ReadSlot {
+  unsigned long long* word = nullptr;
+  int bit = -1;
+  ReadSlot() {
+    std::call_once(g_read_once, [] {
+      void* p = nullptr;
+      hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+      const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+      if (hipHostMalloc(&p, kReadSlots * sizeof(unsigned long long), hipHostMallocPortable) ==
+          hipSuccess)
+        g_read_words = static_cast<unsigned long long*>(p);
+      else
+        (void)hipGetLastError();
+      if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    });
+    if (!g_read_words) return;
+    uint64_t t = g_read_taken.load(std::memory_order_relaxed);
+    while (~t != 0) {
+      const int b = __builtin_ctzll(~t);
+      if (g_read_taken.compare_exchange_weak(t, t | (1ull << b), std::memory_order_acquire)) {
+        bit = b;
+        word = g_read_words + b;
+        return;
+      }
+    }
+  }
+  ~ReadSlot() {
+    if (bit >= 0) g_read_taken.fetch_and(~(1ull << bit), std::memory_order_release);
+  }
+  ReadSlot(const ReadSlot&) = delete;
+  ReadSlot& operator=(const ReadSlot&) = delete;
+};
+
 }  // namespace
 
 extern "C" {
@@ -236,9 +283,12 @@ int32_t abcd_bin_sort(int32_t width, int32_t height, int64_t n, const float* mea
   TRY(launch_bin_sort(width, height, n, means2d, extent, depth, tiles_touched, capacity, workspace,
                       keys_sorted, values_sorted, tile_ranges, tile_order, stream));
   if (n_isect) {
-    unsigned long long m = 0;
-    ABCD_HIP(hipMemcpyAsync(&m, workspace, sizeof m, hipMemcpyDeviceToHost, stream));
+    unsigned long long own = 0;
+    ReadSlot slot;
+    unsigned long long* const word = slot.word ? slot.word : &own;
+    ABCD_HIP(hipMemcpyAsync(word, workspace, sizeof own, hipMemcpyDeviceToHost, stream));
     ABCD_HIP(hipStreamSynchronize(stream));
+    const unsigned long long m = *word;
     *n_isect = (int64_t)m;
     if (m >= (1ull << 32)) {
       set_error("%llu intersections do not fit 32-bit indices", m);

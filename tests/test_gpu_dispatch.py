@@ -219,3 +219,35 @@ def test_binning_small_block_sizes(api, n, size):
     assert np.array_equal(b["values"][:m].cpu().numpy().view(np.uint32), values)
     assert np.array_equal(b["keys"][:m].cpu().numpy().view(np.uint64), keys)
     assert np.array_equal(b["tile_ranges"].cpu().numpy().view(np.uint32), ranges)
+
+
+def test_binning_counts_from_several_threads(api):
+    """The count is read back through words that calls share: threads on streams
+    of their own each get the count of their own block."""
+    import threading
+    from paper_2608_27735_amd.camera import RasterParams, look_at
+    cam = look_at((0.2, -3.0, 0.9), (0, 0, 0), 203, 117)
+    projs, wrong = [], []
+    for n in (300, 900, 2500, 6000):
+        r = S.rng(900 + n)
+        sc = S.gaussians(r, r.uniform(-1, 1, (n, 3)), 0, np.log(0.02), 0.6)
+        projs.append(api.project(cam, RasterParams(sh_degree=0),
+                                 **{k: torch.from_numpy(v).to(dev()) for k, v in sc.items()}))
+    want = [int(p["tiles_touched"].sum()) for p in projs]
+    say("counts from threads", want)
+    torch.cuda.synchronize()
+
+    def work(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for _ in range(20):
+                m = api.bin_sort(cam.width, cam.height, projs[k])["n_isect"]
+                if m != want[k]:
+                    wrong.append((k, m))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(projs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+    assert len(set(want)) == len(want)
