@@ -65,6 +65,9 @@ constexpr int kBlk = 8;                     // block side in tiles
 constexpr int kBlkTiles = kBlk * kBlk;
 constexpr int kCountGrid = 512;             // workgroups of the grid-stride level-2 count
 constexpr int kScatterGrid = 8192;          // workgroups of the grid-stride level-2 scatter
+constexpr uint32_t kXcds = 8;               // workgroup b runs on XCD b % 8
+constexpr uint32_t kXcdRun = 4;             // log2 of the scatter's consecutive sub-chunks per XCD
+static_assert(kScatterGrid % kXcds == 0, "each XCD takes the same number of workgroups");
 constexpr int kRangeParts = 1024;           // most workgroups that look for the keys' range
 constexpr int kRangeItems = 8;              // Gaussians per thread of one of them, or more
 
@@ -1117,6 +1120,15 @@ __global__ __launch_bounds__(64 * kSlice) __attribute__((amdgpu_waves_per_eu(8))
 // (heaviest lists first; on overflow every total is 0, which gives the
 // identity), beside the others' scatter; its buckets go to the dynamic
 // workgroup memory (one byte per tile).
+// Bound by the writes: consecutive sub-chunks continue each other's runs, and
+// where two XCDs meet inside a cache line each writes its part of the line to
+// memory by itself. So an XCD takes 16 (1 << kXcdRun) consecutive sub-chunks,
+// and its own L2 joins the lines between them: 431 -> 378 us for 346.7 M
+// entries of 1080p in 37,344 sub-chunks (3.2 -> 3.7 TB/s), 130 -> 123 us for
+// 49.7 M of 1440p in 27,044, 68.5 -> 66.7 us for 57.2 M in 12,838; 4 and 64
+// sub-chunks took 390 and 379 us on the first. With at most one sub-chunk per
+// workgroup there is nothing to gain (3,304 sub-chunks: 24.6 us in turn, 25.2
+// in runs), and they go round the XCDs one by one.
 __global__ __launch_bounds__(kBlock) void l2_scatter_kernel(
     const unsigned long long* __restrict__ pairs, const float* __restrict__ depth, Geo geo,
     const uint32_t* __restrict__ sub_off, const uint32_t* __restrict__ slice_off,
@@ -1136,7 +1148,10 @@ __global__ __launch_bounds__(kBlock) void l2_scatter_kernel(
   }
   const uint32_t total = hdr->total_sub;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (uint32_t s = blockIdx.x; s < total; s += gridDim.x) {
+  const uint32_t run = total > (uint32_t)kScatterGrid ? kXcdRun : 0u;
+  for (uint32_t j = blockIdx.x / kXcds;; j += gridDim.x / kXcds) {
+    const uint32_t s = (((j >> run) * kXcds + blockIdx.x % kXcds) << run) + (j & ((1u << run) - 1u));
+    if (s >= total) break;  // s grows with j
     uint32_t subb, soff;
     const SubChunk sc =
         sub_chunk_of(s, block_of_wave(s, sub_off, slice_off, geo.nblk, subb, soff), sub_off, blk_off, geo);
