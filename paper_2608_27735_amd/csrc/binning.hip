@@ -23,10 +23,13 @@
 // entry into a different line and pays several times the payload in HBM
 // writes).
 //
-//   bin_zero               header, counters and look-back states
-//   depth_keys             keys, tile rectangles, digit counts, block totals,
-//                          intersection count M
-//   radix_pass x4          depth order of the n Gaussians
+//   bin_zero               header, counters and look-back states cleared; the
+//                          range of the visible Gaussians' depths
+//   depth_keys             keys (counted from the smallest depth), tile
+//                          rectangles, digit counts, block totals,
+//                          intersection count M, radix passes needed
+//   radix_pass x4          depth order of the n Gaussians (a pass over digits
+//                          that the range leaves all zero returns at once)
 //   l1_place               (block, Gaussian) pairs, bucket-major, depth order;
 //                          bucket offsets, sub-chunk and slice tables,
 //                          overflow flag (on overflow nothing is placed: every
@@ -37,6 +40,9 @@
 //                          last: tile_ranges
 //   l2_scatter             values (and keys), tile-major, depth order; its
 //                          first workgroup: the forward's tile order
+//
+// A call with no room for any entry (capacity 0) only counts M, and small
+// blocks take two launches of their own (below).
 #include <atomic>
 
 #include <algorithm>
@@ -102,8 +108,8 @@ inline Geo geo_of(int width, int height) {
 }
 
 struct WsLayout {
-  size_t range, hdr, ghist, mcopy, bcopy, blk_done, lb1, st0, st1, keys_a, keys_b, vals_a, vals_b, rects, blk_off,
-      sub_off, slice_off, pairs, c2, slice_tot, tile_total, tile_off, total;
+  size_t range, hdr, ghist, mcopy, bcopy, blk_done, lb1, st0, st1, keys_a, keys_b, vals_a, vals_b,
+      rects, blk_off, sub_off, slice_off, pairs, c2, slice_tot, tile_total, tile_off, total;
   int64_t rs_parts, chunks, max_sub, max_slices;
 };
 
@@ -630,7 +636,8 @@ __device__ __forceinline__ uint32_t slices_of(uint32_t s0, uint32_t s1) {
 
 __global__ __launch_bounds__(256) void l1_place_kernel(
     int64_t n, const uint32_t* __restrict__ order_even, const uint32_t* __restrict__ order_odd,
-    const unsigned long long* __restrict__ rects, Geo geo, const uint32_t* __restrict__ bcopy, const unsigned long long* __restrict__ mcopy,
+    const unsigned long long* __restrict__ rects, Geo geo,
+    const uint32_t* __restrict__ bcopy, const unsigned long long* __restrict__ mcopy,
     unsigned long long capacity, int64_t chunks, uint32_t* __restrict__ lb,
     uint32_t* __restrict__ blk_off, uint32_t* __restrict__ sub_off, uint32_t* __restrict__ slice_off,
     WsHeader* __restrict__ hdr, unsigned long long* __restrict__ pairs,

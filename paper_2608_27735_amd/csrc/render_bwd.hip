@@ -155,8 +155,8 @@ __device__ __forceinline__ void bwd_item(
     const uint32_t* __restrict__ values, const float2* __restrict__ means2d,
     const float4* __restrict__ conic_opacity, const float* __restrict__ rgb,
     const float4* __restrict__ F, const float4* __restrict__ B, const float* __restrict__ final_T,
-    const uint32_t* __restrict__ last, const float4* __restrict__ dL_dout, const uint32_t* __restrict__ walk, float* __restrict__ g2d,
-    const SplitLayout& sp) {
+    const uint32_t* __restrict__ last, const float4* __restrict__ dL_dout,
+    const uint32_t* __restrict__ walk, float* __restrict__ g2d, const SplitLayout& sp) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int px = (tile % k.ntx) * kTile + quad_x(tid);
@@ -620,7 +620,7 @@ __global__ __launch_bounds__(256) void render_bwd_direct_kernel(
 
 static_assert(kQueueStride * kQueues == 64 * 8, "queue block of bwd_workspace_bytes");
 
-// g2d (field-major), then the backward's tile work, tile order, work items (when
+// g2d ([n][9]), then the backward's tile work, tile order, work items (when
 // not split) and queue.
 size_t render_bwd_workspace_bytes(int64_t n) { return bwd_workspace_bytes(n); }
 

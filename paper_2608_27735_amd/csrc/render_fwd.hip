@@ -81,9 +81,10 @@ __device__ __forceinline__ int stage_fwd(FwdLds& s, const Rec& rec, uint32_t rea
 // pixel's transmittance is the smallest of the rows' last blended values).
 template <bool kHalf>
 __device__ __forceinline__ void fwd_rows(
-    FwdLds& s, const BlendConsts& k, const uint32_t* __restrict__ tile_ranges, const uint32_t* __restrict__ values,
-    const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
-    const float* __restrict__ rgb, const float4* __restrict__ F, const float4* __restrict__ B,
+    FwdLds& s, const BlendConsts& k, const uint32_t* __restrict__ tile_ranges,
+    const uint32_t* __restrict__ values, const float2* __restrict__ means2d,
+    const float4* __restrict__ conic_opacity, const float* __restrict__ rgb,
+    const float4* __restrict__ F, const float4* __restrict__ B,
     float4* __restrict__ out, float* __restrict__ final_T, uint32_t* __restrict__ last,
     unsigned long long* __restrict__ n_blends, uint2* __restrict__ out16, int* __restrict__ rect,
     int fb_stop, const SplitLayout& sp) {
