@@ -265,8 +265,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
   __shared__ FwdLds s;
   if (kFew) {
     if (tile_ranges[2 * k.ntiles - 1] <= kFewPairs) {  // the number of pairs
-      fwd_rows<kHalf>(s, k, tile_ranges, values, means2d, conic_opacity, rgb, F, B, out, final_T,
-                      last, n_blends, out16, rect, fb_stop, sp);
+      // the general layout without an order rounds its workgroups up to eight,
+      // more than four per tile of a frame of one tile
+      if ((int)blockIdx.x < 4 * k.ntiles)
+        fwd_rows<kHalf>(s, k, tile_ranges, values, means2d, conic_opacity, rgb, F, B, out, final_T,
+                        last, n_blends, out16, rect, fb_stop, sp);
       return;
     }
     if ((int)blockIdx.x >= few) return;

@@ -251,3 +251,37 @@ def test_binning_counts_from_several_threads(api):
         t.join()
     assert not wrong
     assert len(set(want)) == len(want)
+
+
+@pytest.mark.parametrize("size", [(16, 16), (9, 7), (32, 16), (33, 9)])
+def test_split_of_a_few_tiles_without_an_order(api, size):
+    """A split forward of one, two and three tiles with no tile order: the grid is
+    rounded up to eight workgroups, of which those past the last tile do nothing.
+    Parity bars against the oracle, for lists longer than a chunk."""
+    from paper_2608_27735_amd.camera import RasterParams, look_at
+    r = S.rng(1000 + size[0])
+    cam = look_at((0.0, -3.0, 0.0), (0, 0, 0), *size, fov_x_deg=20.0)
+    prm = RasterParams(sh_degree=0)
+    sc = S.gaussians(r, r.uniform(-0.4, 0.4, (900, 3)), 0, np.log(0.05), 0.4)
+    sc["opacity_logits"] -= 4.0  # faint, so that the walks cross the chunks
+    F, B = S.background_pair(r, cam.height, cam.width)
+    say("split without an order", size)
+    ref = O.step(cam, prm, sc, F=F, B=B, rel_margin=1e-4)
+    knife = ref["fwd"]["knife"]
+    dL = np.where(knife[..., None], 0, S.upstream_grad(r, cam.height, cam.width)).astype(np.float32)
+    ref = O.step(cam, prm, sc, F=F, B=B, dL_dout=dL.astype(np.float64), rel_margin=1e-4)
+    d = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to(dev())
+    params = {k: d(v) for k, v in sc.items()}
+    proj = api.project(cam, prm, **params)
+    bins = api.bin_sort(cam.width, cam.height, proj)
+    bins["tile_order"] = None
+    split = api.make_split(bins["n_isect"] // 256 + api.n_tiles(*size) + 1, 256)
+    fwd = api.render_fwd(cam, prm, bins, proj, F=d(F), B=d(B), split=split)
+    grads = api.render_bwd(cam, prm, params, proj, bins, fwd, d(dL), F=d(F), B=d(B), split=split)
+    torch.cuda.synchronize()
+    assert np.abs(fwd["out"].cpu().numpy() - ref["fwd"]["out"])[~knife].max() <= 1e-5
+    assert np.array_equal(fwd["last"].cpu().numpy().view(np.uint32)[~knife],
+                          ref["fwd"]["last"][~knife])
+    for k in params:
+        g, gr = grads[k].cpu().numpy().astype(np.float64), ref["grads"][k]
+        assert np.linalg.norm(g - gr) <= 1e-4 * max(np.linalg.norm(gr), 1e-30), k
