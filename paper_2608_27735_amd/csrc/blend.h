@@ -222,13 +222,17 @@ __device__ __forceinline__ int quad_slots(uint32_t quads, int (*s_cnt)[4], int (
 // wave and four list entries per step of a wave.
 constexpr int kRowsTiles = 256;
 
-// Frames of at most kFewTiles tiles (without a split) take the same layout when
-// their lists hold at most kFewPairs (tile, Gaussian) pairs, which only the GPU
-// knows: both layouts are in the kernel, the workgroups of four per tile are
-// launched, and those the chosen layout has no use for return. With so few
-// pairs the whole chip would blend them in 10 us and the longest list sets the
-// launch's length (1,024 Gaussians over 56 of 1,024 tiles: backward 75 -> 43 us,
-// forward 35 -> 32).
+// Frames of at most kFewTiles tiles (without a split) take the same layout in the
+// backward when their lists hold at most kFewPairs (tile, Gaussian) pairs, which
+// only the GPU knows: both layouts are in the kernel, the workgroups of four per
+// tile are launched, and those the chosen layout has no use for return. With so
+// few pairs the whole chip would blend them in 10 us and the longest list sets the
+// launch's length (1,024 Gaussians over 56 of 1,024 tiles: 75 -> 43 us). The
+// forward of such a frame keeps one workgroup per tile: the rows layout brought a
+// few us where the lists are long (1,024 Gaussians over 149 of 1,024 tiles 31 ->
+// 26) and cost 12 to 28 where they are spread out (over 864 of 1,024 tiles 20 ->
+// 48, 8,192 Gaussians over 769 20 -> 43), and its outputs would no longer be the
+// split forward's bit by bit.
 constexpr int kFewTiles = 1024;
 constexpr uint32_t kFewPairs = 65536;
 

@@ -80,14 +80,14 @@ __device__ __forceinline__ int stage_fwd(FwdLds& s, const Rec& rec, uint32_t rea
 // of its own entries; the four rows are combined once, at the end (the
 // pixel's transmittance is the smallest of the rows' last blended values).
 template <bool kHalf>
-__device__ __forceinline__ void fwd_rows(
-    FwdLds& s, const BlendConsts& k, const uint32_t* __restrict__ tile_ranges,
-    const uint32_t* __restrict__ values, const float2* __restrict__ means2d,
-    const float4* __restrict__ conic_opacity, const float* __restrict__ rgb,
-    const float4* __restrict__ F, const float4* __restrict__ B,
+__global__ __launch_bounds__(256) void render_fwd_rows_kernel(
+    BlendConsts k, const uint32_t* __restrict__ tile_ranges, const uint32_t* __restrict__ values,
+    const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
+    const float* __restrict__ rgb, const float4* __restrict__ F, const float4* __restrict__ B,
     float4* __restrict__ out, float* __restrict__ final_T, uint32_t* __restrict__ last,
     unsigned long long* __restrict__ n_blends, uint2* __restrict__ out16, int* __restrict__ rect,
-    int fb_stop, const SplitLayout& sp) {
+    int fb_stop) {
+  __shared__ FwdLds s;
   const int tile = (int)(blockIdx.x >> 2), quarter = (int)(blockIdx.x & 3);
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, col = lane & 15, e = lane >> 4;
   const int px = (tile % k.ntx) * kTile + col;
@@ -189,18 +189,6 @@ __device__ __forceinline__ void fwd_rows(
     const Swapped k2 = swap_bit5(__uint_as_float(l1));
     lastk = max(__float_as_uint(k2.first), __float_as_uint(k2.second));
   }
-  if (!kHalf && sp.ckpt) {
-    // no tile is split; its walk and work estimate are the largest of the
-    // quarters' (cleared before the launch)
-    uint32_t m = lastk;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
-    if (lane == 0 && m) {
-      atomicMax(&sp.walk[tile], m);
-      atomicMax(&sp.work[tile], m);
-    }
-    if (quarter == 0 && tid == 0) sp.slot_of[(size_t)tile * kMaxChunks] = kNoSlot;
-  }
   if (kHalf && rect) {
     // coverage of the cached image: tiles holding any pixel that blended
     if (__syncthreads_or(inside && T < 1.0f) && tid == 0) {
@@ -235,45 +223,18 @@ __device__ __forceinline__ void fwd_rows(
   }
 }
 
-template <bool kHalf>
-__global__ __launch_bounds__(256) void render_fwd_rows_kernel(
-    BlendConsts k, const uint32_t* __restrict__ tile_ranges, const uint32_t* __restrict__ values,
-    const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
-    const float* __restrict__ rgb, const float4* __restrict__ F, const float4* __restrict__ B,
-    float4* __restrict__ out, float* __restrict__ final_T, uint32_t* __restrict__ last,
-    unsigned long long* __restrict__ n_blends, uint2* __restrict__ out16, int* __restrict__ rect,
-    int fb_stop) {
-  __shared__ FwdLds s;
-  fwd_rows<kHalf>(s, k, tile_ranges, values, means2d, conic_opacity, rgb, F, B, out, final_T, last,
-                  n_blends, out16, rect, fb_stop, SplitLayout{});
-}
-
 // kHalf: the cached-render variant: F = B = transparent, the image is written
 // as fp16 RGBA to out16 (round to nearest even), no final T or walk lengths.
-// kFew: a frame that may take the rows layout (see kFewPairs); few is then the
-// number of workgroups of the general one. (In the one kernel for all frames the
-// extra code cost the large ones 2%.)
 // Register budget: four waves per SIMD (at most 128 VGPRs).
-template <bool kHalf, bool kFew>
+template <bool kHalf>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void render_fwd_kernel(
     BlendConsts k, const uint32_t* __restrict__ tile_ranges, const uint32_t* __restrict__ values,
     const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
     const float* __restrict__ rgb, const float4* __restrict__ F, const float4* __restrict__ B,
     float4* __restrict__ out, float* __restrict__ final_T, uint32_t* __restrict__ last,
     unsigned long long* __restrict__ n_blends, const uint32_t* __restrict__ order,
-    uint2* __restrict__ out16, int* __restrict__ rect, int fb_stop, SplitLayout sp, int few) {
+    uint2* __restrict__ out16, int* __restrict__ rect, int fb_stop, SplitLayout sp) {
   __shared__ FwdLds s;
-  if (kFew) {
-    if (tile_ranges[2 * k.ntiles - 1] <= kFewPairs) {  // the number of pairs
-      // the general layout without an order rounds its workgroups up to eight,
-      // more than four per tile of a frame of one tile
-      if ((int)blockIdx.x < 4 * k.ntiles)
-        fwd_rows<kHalf>(s, k, tile_ranges, values, means2d, conic_opacity, rgb, F, B, out, final_T,
-                        last, n_blends, out16, rect, fb_stop, sp);
-      return;
-    }
-    if ((int)blockIdx.x >= few) return;
-  }
   const int tile = tile_of_block(k, order);
   if ((unsigned)tile >= (unsigned)k.ntiles) return;
   const int tid = threadIdx.x;
@@ -507,14 +468,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
   }
 }
 
-// Before a forward that splits: no slot taken; in frames that may take the rows
-// layout, no walk of any tile yet.
-__global__ __launch_bounds__(256) void split_clear_kernel(SplitLayout sp, int tiles) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < 16) sp.hdr[i] = 0u;
-  if (i < tiles) sp.work[i] = sp.walk[i] = 0u;
-}
-
 __global__ void rect_init_kernel(int* __restrict__ rect, int width, int height) {
   if (threadIdx.x == 0) {
     rect[0] = width;
@@ -544,24 +497,13 @@ int32_t launch_render_fwd(const abcd_camera& cam, const abcd_raster_params& prm,
     ABCD_HIP(hipGetLastError());
     return ABCD_OK;
   }
-  const int few = k.ntiles <= kFewTiles ? grid : 0;
-  if (split.ckpt) {
-    const int tiles = few ? k.ntiles : 0;
-    ABCD_LAUNCH("zero_fill", split_clear_kernel, std::max(1, (tiles + 255) / 256), 256, 0, stream,
-                split, tiles);
-  }
-#define ABCD_FWD(kFew, blocks)                                                                    \
-  ABCD_LAUNCH("render_fwd", (render_fwd_kernel<false, kFew>), blocks, kBlock, 0, stream, k,       \
-              tile_ranges, values_sorted, reinterpret_cast<const float2*>(means2d),               \
-              reinterpret_cast<const float4*>(conic_opacity), rgb,                                \
-              reinterpret_cast<const float4*>(F), reinterpret_cast<const float4*>(B),             \
-              reinterpret_cast<float4*>(out_rgba), final_T, last, n_blends, tile_order, nullptr,  \
-              nullptr, (int)(prm.flags & ABCD_FLAG_FB_STOP), split, few)
-  if (few)
-    ABCD_FWD(true, std::max(grid, 4 * k.ntiles));
-  else
-    ABCD_FWD(false, grid);
-#undef ABCD_FWD
+  if (split.ckpt) TRY_STATUS(launch_zero(reinterpret_cast<float*>(split.hdr), 16, stream));
+  ABCD_LAUNCH("render_fwd", render_fwd_kernel<false>, grid, kBlock, 0, stream, k, tile_ranges,
+              values_sorted, reinterpret_cast<const float2*>(means2d),
+              reinterpret_cast<const float4*>(conic_opacity), rgb,
+              reinterpret_cast<const float4*>(F), reinterpret_cast<const float4*>(B),
+              reinterpret_cast<float4*>(out_rgba), final_T, last, n_blends, tile_order, nullptr,
+              nullptr, (int)(prm.flags & ABCD_FLAG_FB_STOP), split);
   ABCD_HIP(hipGetLastError());
   return ABCD_OK;
 }
@@ -585,18 +527,11 @@ int32_t launch_render_cache(const abcd_camera& cam, const abcd_raster_params& pr
     ABCD_HIP(hipGetLastError());
     return ABCD_OK;
   }
-  const int few = k.ntiles <= kFewTiles ? grid : 0;
-#define ABCD_CACHE(kFew, blocks)                                                                  \
-  ABCD_LAUNCH("render_cache", (render_fwd_kernel<true, kFew>), blocks, kBlock, 0, stream, k,      \
-              tile_ranges, values_sorted, reinterpret_cast<const float2*>(means2d),               \
-              reinterpret_cast<const float4*>(conic_opacity), rgb, nullptr, nullptr, nullptr,     \
-              nullptr, nullptr, nullptr, tile_order, reinterpret_cast<uint2*>(image_f16), rect,   \
-              0, SplitLayout{}, few)
-  if (few)
-    ABCD_CACHE(true, std::max(grid, 4 * k.ntiles));
-  else
-    ABCD_CACHE(false, grid);
-#undef ABCD_CACHE
+  ABCD_LAUNCH("render_cache", render_fwd_kernel<true>, grid, kBlock, 0, stream, k, tile_ranges,
+              values_sorted, reinterpret_cast<const float2*>(means2d),
+              reinterpret_cast<const float4*>(conic_opacity), rgb, nullptr, nullptr, nullptr,
+              nullptr, nullptr, nullptr, tile_order, reinterpret_cast<uint2*>(image_f16), rect, 0,
+              SplitLayout{});
   ABCD_HIP(hipGetLastError());
   return ABCD_OK;
 }

@@ -285,3 +285,37 @@ def test_split_of_a_few_tiles_without_an_order(api, size):
     for k in params:
         g, gr = grads[k].cpu().numpy().astype(np.float64), ref["grads"][k]
         assert np.linalg.norm(g - gr) <= 1e-4 * max(np.linalg.norm(gr), 1e-30), k
+
+
+@pytest.mark.parametrize("size", [(48, 48), (272, 256)])
+def test_split_takes_slots_of_few_pairs(api, size):
+    """A split forward takes a checkpoint slot for every chunk boundary that a walk
+    crosses and one for the end of each tile split, however few pairs the lists
+    hold in all; above 256 tiles its outputs are the unsplit ones bit by bit."""
+    from paper_2608_27735_amd.camera import RasterParams, look_at
+    r = S.rng(1100)
+    cam = look_at((0.0, -3.0, 0.0), (0, 0, 0), *size)
+    prm = RasterParams(sh_degree=0)
+    sc = S.gaussians(r, r.uniform(-0.05, 0.05, (3000, 3)), 0, np.log(0.01), 0.3)
+    sc["opacity_logits"] -= 5.0  # faint: the walks run through several chunks
+    d = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to(dev())
+    params = {k: d(v) for k, v in sc.items()}
+    proj = api.project(cam, prm, **params)
+    bins = api.bin_sort(cam.width, cam.height, proj)
+    say("slots of few pairs", size, bins["n_isect"])
+    assert bins["n_isect"] <= 65536
+    split = api.make_split(bins["n_isect"] // 256 + api.n_tiles(*size) + 1, 256)
+    fwd = api.render_fwd(cam, prm, bins, proj, split=split)
+    whole = api.render_fwd(cam, prm, bins, proj)
+    torch.cuda.synchronize()
+    nty, ntx = (size[1] + 15) // 16, (size[0] + 15) // 16
+    pad = np.zeros((16 * nty, 16 * ntx), np.int64)
+    pad[:size[1], :size[0]] = fwd["last"].cpu().numpy()
+    walk = pad.reshape(nty, 16, ntx, 16).max(axis=(1, 3))  # a lower bound: walks end past it
+    crossed = np.maximum(walk - 1, 0) // 256
+    assert crossed.max() >= 3
+    taken = int(split["workspace"][:4].view(torch.int32))
+    assert taken >= int(crossed.sum() + (crossed > 0).sum())
+    if api.n_tiles(*size) > 256:
+        for k in ("out", "final_T", "last"):
+            assert torch.equal(fwd[k], whole[k])
