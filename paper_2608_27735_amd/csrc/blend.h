@@ -222,19 +222,29 @@ __device__ __forceinline__ int quad_slots(uint32_t quads, int (*s_cnt)[4], int (
 // wave and four list entries per step of a wave.
 constexpr int kRowsTiles = 256;
 
-// Frames of at most kFewTiles tiles (without a split) take the same layout in the
-// backward when their lists hold at most kFewPairs (tile, Gaussian) pairs, which
-// only the GPU knows: both layouts are in the kernel, the workgroups of four per
-// tile are launched, and those the chosen layout has no use for return. With so
-// few pairs the whole chip would blend them in 10 us and the longest list sets the
-// launch's length (1,024 Gaussians over 56 of 1,024 tiles: 75 -> 43 us). The
-// forward of such a frame keeps one workgroup per tile: the rows layout brought a
-// few us where the lists are long (1,024 Gaussians over 149 of 1,024 tiles 31 ->
-// 26) and cost 12 to 28 where they are spread out (over 864 of 1,024 tiles 20 ->
-// 48, 8,192 Gaussians over 769 20 -> 43), and its outputs would no longer be the
-// split forward's bit by bit.
+// In frames of at most kFewTiles tiles (without a split) whose lists hold at most
+// kFewPairs (tile, Gaussian) pairs, the backward takes a list of at least
+// kRowsList entries in the same layout and a shorter one whole. Only the GPU
+// knows the lists: a workgroup for each whole tile and four for its rows are
+// launched, and those that the tile's list has no use for return. With so few
+// pairs the whole chip would blend them in 10 us and the longest list sets the
+// launch's length. Each limit with both sides measured, in us, on 1,024 tiles:
+//   whole / rows: 1,024 Gaussians, longest list 718: 68 / 46; 16,000, longest
+//   1,862: 178 / 79;
+//   lists from 96 / 128 / 192 on in rows: 8,192 Gaussians over 769 tiles, longest
+//   list 185: 44 / 41 / 31 (whole 40), longest 611 over 206 tiles: 53 / 58 / 59;
+//   512 on 272 tiles, longest 222: 19 / 23 / 27 (whole 38). All lists in rows
+//   cost frames with many short ones: 1,024 over 675 tiles, longest 29, 15 -> 24.
+// The pairs' limit: 62,753 pairs over 61 tiles take 107 in rows, 274 whole; 84,814
+// over 917 tiles 63 in rows, 45 whole.
+// The forward keeps one workgroup per tile in such frames: the rows layout
+// brought a few us where the lists are long (1,024 Gaussians over 149 of 1,024
+// tiles 31 -> 26) and cost 12 to 28 where they are spread out (over 864 of 1,024
+// tiles 20 -> 48, 8,192 Gaussians over 769 20 -> 43), and its outputs would no
+// longer be the split forward's bit by bit.
 constexpr int kFewTiles = 1024;
 constexpr uint32_t kFewPairs = 65536;
+constexpr uint32_t kRowsList = 128;
 
 // Lane-bit-4 and lane-bit-5 exchanges. v_permlane16_swap of (x, x) leaves
 // rows (0, 0, 2, 2) of x in its first result and rows (1, 1, 3, 3) in its

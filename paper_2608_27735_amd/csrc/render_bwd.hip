@@ -437,13 +437,12 @@ __device__ __forceinline__ int rowsum9_slot(int c) {
 // alpha-derivative is T (c . g) - (S + T_final g_T) / (1 - alpha).
 
 __device__ __forceinline__ void bwd_rows(
-    BwdLds& s, const BlendConsts& k, const uint32_t* __restrict__ tile_ranges,
+    BwdLds& s, const BlendConsts& k, int tile, int quarter, const uint32_t* __restrict__ tile_ranges,
     const uint32_t* __restrict__ values,
     const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
     const float* __restrict__ rgb, const float4* __restrict__ F, const float4* __restrict__ B,
     const float* __restrict__ final_T, const uint32_t* __restrict__ last,
     const float4* __restrict__ dL_dout, float* __restrict__ g2d) {
-  const int tile = (int)(blockIdx.x >> 2), quarter = (int)(blockIdx.x & 3);
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, e = lane >> 4;
   const int px = (tile % k.ntx) * kTile + col;
   const int py = (tile / k.ntx) * kTile + 4 * quarter + (tid >> 6);
@@ -595,12 +594,13 @@ __global__ __launch_bounds__(256) void render_bwd_rows_kernel(
     const float* __restrict__ final_T, const uint32_t* __restrict__ last,
     const float4* __restrict__ dL_dout, float* __restrict__ g2d) {
   __shared__ BwdLds s;
-  bwd_rows(s, k, tile_ranges, values, means2d, conic_opacity, rgb, F, B, final_T, last, dL_dout, g2d);
+  bwd_rows(s, k, (int)(blockIdx.x >> 2), (int)(blockIdx.x & 3), tile_ranges, values, means2d,
+           conic_opacity, rgb, F, B, final_T, last, dL_dout, g2d);
 }
 
 // Unsplit frames of at most kDirectTiles tiles, without the schedule's two
-// launches: one workgroup per tile in raster order, or, with few pairs, four
-// (see kFewPairs).
+// launches, in raster order: the first workgroups take a tile each, then come four
+// per tile for the lists that are taken in rows (see kRowsList).
 __global__ __launch_bounds__(256) void render_bwd_direct_kernel(
     BlendConsts k, const uint32_t* __restrict__ tile_ranges, const uint32_t* __restrict__ values,
     const float2* __restrict__ means2d, const float4* __restrict__ conic_opacity,
@@ -608,12 +608,17 @@ __global__ __launch_bounds__(256) void render_bwd_direct_kernel(
     const float* __restrict__ final_T, const uint32_t* __restrict__ last,
     const float4* __restrict__ dL_dout, float* __restrict__ g2d) {
   __shared__ BwdLds s;
-  if (tile_ranges[2 * k.ntiles - 1] <= kFewPairs)
-    bwd_rows(s, k, tile_ranges, values, means2d, conic_opacity, rgb, F, B, final_T, last, dL_dout,
-             g2d);
-  else if ((int)blockIdx.x < k.ntiles)
-    bwd_item<true>(s, k, (int)blockIdx.x, 0u, tile_ranges, values, means2d, conic_opacity, rgb, F, B,
-                   final_T, last, dL_dout, nullptr, g2d, SplitLayout{});
+  const bool few = tile_ranges[2 * k.ntiles - 1] <= kFewPairs;
+  const int b = (int)blockIdx.x, r = b - k.ntiles;
+  const int tile = r < 0 ? b : r >> 2;
+  const bool rows = few && tile_ranges[2 * tile + 1] - tile_ranges[2 * tile] >= kRowsList;
+  if (rows != (r >= 0)) return;
+  if (rows)
+    bwd_rows(s, k, tile, r & 3, tile_ranges, values, means2d, conic_opacity, rgb, F, B, final_T,
+             last, dL_dout, g2d);
+  else
+    bwd_item<true>(s, k, tile, 0u, tile_ranges, values, means2d, conic_opacity, rgb, F, B, final_T,
+                   last, dL_dout, nullptr, g2d, SplitLayout{});
 }
 
 }  // namespace
@@ -663,7 +668,7 @@ int32_t launch_render_bwd_pixels(const abcd_camera& cam, const abcd_raster_param
                   reinterpret_cast<const float4*>(F), reinterpret_cast<const float4*>(B), final_T,
                   last, reinterpret_cast<const float4*>(dL_dout), g2d);
     else
-      ABCD_LAUNCH("render_bwd", render_bwd_direct_kernel, 4 * k.ntiles, kBlock, 0, stream, k,
+      ABCD_LAUNCH("render_bwd", render_bwd_direct_kernel, 5 * k.ntiles, kBlock, 0, stream, k,
                   tile_ranges, values_sorted, reinterpret_cast<const float2*>(means2d),
                   reinterpret_cast<const float4*>(conic_opacity), rgb,
                   reinterpret_cast<const float4*>(F), reinterpret_cast<const float4*>(B), final_T,

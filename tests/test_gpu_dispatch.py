@@ -319,3 +319,10 @@ def test_split_takes_slots_of_few_pairs(api, size):
     if api.n_tiles(*size) > 256:
         for k in ("out", "final_T", "last"):
             assert torch.equal(fwd[k], whole[k])
+
+
+@pytest.mark.parametrize("count", [127, 128, 129])
+def test_backward_lists_about_the_rows_limit(api, count):
+    """Lists one short of, at and one past the length from which the backward of an
+    unsplit frame of 272 tiles gives a tile four workgroups instead of one."""
+    test_forward_list_lengths(api, count, -4.0)
