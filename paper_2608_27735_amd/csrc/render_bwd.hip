@@ -18,6 +18,14 @@ __device__ __forceinline__ float dpp_mov(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xF, 0xF, true));
 }
 
+// A product whose result is zero where either factor is, whatever the other holds
+// (v_mul_legacy_f32; the plain product otherwise). The weight of an entry that a
+// pixel does not blend is zero, and so the NaN or infinity that the upstream
+// gradient may hold at that pixel stays out of the entry's sums, for the price of
+// a plain product.
+extern "C" __device__ __attribute__((const)) float mul_zero_wins(float, float) __asm(
+    "llvm.amdgcn.fmul.legacy");
+
 // The sums over a wave's 8x8 pixels of the nine gradient values of four list
 // entries. Lane l is pixel (l & 7, l >> 3) of the quadrant, so the column
 // factor dx of a moment is common to a lane's column: the pixels' rows are
@@ -330,9 +338,9 @@ __device__ __forceinline__ void bwd_item(
       const float iom = __builtin_amdgcn_rcpf(1.0f - a);  // 1 - a >= 1 - alpha_max > 0
       T *= iom;  // before the entry
       const float wgt = a * T;
-      gr[12 + i] = wgt * gcr;
-      gr[16 + i] = wgt * gcg;
-      gr[20 + i] = wgt * gcb;
+      gr[12 + i] = mul_zero_wins(wgt, gcr);
+      gr[16 + i] = mul_zero_wins(wgt, gcg);
+      gr[20 + i] = mul_zero_wins(wgt, gcb);
       const float D = fmaf(gcv[i].x, gcb, fmaf(gbv[i].w, gcg, fmaf(gbv[i].z, gcr, -RG)));
       const float dLda = T * D - iom * TgT;
       RG = fmaf(a, D, RG);
@@ -572,9 +580,9 @@ __device__ __forceinline__ void bwd_rows(
       gr[3] = q * dy;
       gr[4] = r * dy;
       gr[5] = gp;
-      gr[6] = wgt * gcr;
-      gr[7] = wgt * gcg;
-      gr[8] = wgt * gcb;
+      gr[6] = mul_zero_wins(wgt, gcr);
+      gr[7] = mul_zero_wins(wgt, gcg);
+      gr[8] = mul_zero_wins(wgt, gcb);
       float v8;
       const float m = row_sum9(gr, col, v8);
       float out = col == 1 ? v8 : m;

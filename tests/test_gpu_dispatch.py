@@ -326,3 +326,52 @@ def test_backward_lists_about_the_rows_limit(api, count):
     """Lists one short of, at and one past the length from which the backward of an
     unsplit frame of 272 tiles gives a tile four workgroups instead of one."""
     test_forward_list_lengths(api, count, -4.0)
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+@pytest.mark.parametrize("at", ["middle", "edge"])
+@pytest.mark.parametrize("size", [(203, 117), (270, 250), (523, 507)])
+def test_backward_upstream_not_finite_stays_with_the_pixel(api, size, at, bad):
+    """A NaN or an infinity in one pixel's upstream gradient reaches the Gaussians
+    that this pixel blends and no other: not those that its wave or its group of
+    four blends elsewhere, and, at the first pixel of a tile that the frame's edge
+    cuts, nothing through the tile's pixels outside the frame. On 104 tiles (four
+    workgroups a tile), 272 (one, without a schedule) and 1,056 (the queue)."""
+    from paper_2608_27735_amd.camera import RasterParams, look_at
+    r = S.rng(1200)
+    cam = look_at((0.0, -3.0, 0.0), (0, 0, 0), *size)
+    pos = np.stack([r.uniform(-1.8, 1.8, 4001), r.uniform(-0.5, 0.5, 4001), r.uniform(-1.8, 1.8, 4001)], 1)
+    sc = S.gaussians(r, pos, 0, np.log(0.03), 0.5)
+    prm = RasterParams(sh_degree=0)
+    x, y = ((size[0] // 2, size[1] // 2) if at == "middle" else
+            ((size[0] - 1) // 16 * 16, (size[1] - 1) // 16 * 16))
+    say("not finite upstream", size, at, bad, x, y)
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev())
+    params = {k: d(v) for k, v in sc.items()}
+    proj = api.project(cam, prm, **params)
+    bins = api.bin_sort(cam.width, cam.height, proj)
+    fwd = api.render_fwd(cam, prm, bins, proj)
+    dL = S.upstream_grad(r, cam.height, cam.width)
+    clean = api.render_bwd(cam, prm, params, proj, bins, fwd, d(dL))
+    dL[y, x] = bad
+    got = api.render_bwd(cam, prm, params, proj, bins, fwd, d(dL))
+    torch.cuda.synchronize()
+    # alphas of the pixel's walk in 64 bits
+    ntx = (cam.width + 15) // 16
+    a, _ = bins["tile_ranges"].cpu().numpy()[y // 16 * ntx + x // 16]
+    walk = bins["values"].cpu().numpy()[a:a + int(fwd["last"][y, x])]
+    u, v = proj["means2d"].cpu().numpy()[walk].astype(np.float64).T
+    l11, l21, l22, o = proj["conic_opacity"].cpu().numpy()[walk].astype(np.float64).T
+    dx, dy = x + 0.5 - u, y + 0.5 - v
+    alpha = o * np.exp(-0.5 * ((l11 * dx + l21 * dy) ** 2 + (l22 * dy) ** 2))
+    blended, near = np.zeros(4001, bool), np.zeros(4001, bool)
+    blended[walk[alpha >= prm.alpha_min * (1 + 1e-4)]] = True
+    near[walk[alpha >= prm.alpha_min * (1 - 1e-4)]] = True
+    assert 0 < blended.sum() < len(walk)
+    # the colour of a Gaussian that the pixel blends takes the pixel's gradient
+    assert not torch.isfinite(got["sh"]).reshape(4001, -1).all(1).cpu().numpy()[blended].any()
+    for k in params:
+        g, c = got[k].cpu().numpy().reshape(4001, -1), clean[k].cpu().numpy().reshape(4001, -1)
+        assert np.isfinite(g[~near]).all(), (k, int((~np.isfinite(g[~near]).all(1)).sum()))
+        # the order of the atomic adds differs between the two calls
+        assert np.linalg.norm(g[~near] - c[~near]) <= 1e-5 * np.linalg.norm(c), k
