@@ -81,15 +81,14 @@ __device__ __forceinline__ bool tile_rect(float u, float v, float rx, float ry, 
 
 // A screen-space Gaussian as the blend kernels stage it in LDS: the conic is
 // pre-scaled so that (qa dx + qb dy)^2 + (qc dy)^2 = -power * log2(e), and alpha
-// is one v_exp_f32 away.
-constexpr float kLog2e = 1.4426950408889634f;
+// is one v_exp_f32 and a product away.
 
 // conic_opacity holds (l11, l21, l22, o): the conic [[a, b], [b, c]] as its
 // Cholesky factor L = [[l11, 0], [l21, l22]], and the opacity.
 struct Splat {
   float u, v;          // mean
   float qa, qb, qc;    // s l11, s l21, s l22 with s^2 = log2(e) / 2
-  float lo;            // log2 of the opacity
+  float o;             // opacity
 };
 
 constexpr float kHalfLog2eSqrt = 0.84932180028801904f;  // sqrt(log2(e) / 2)
@@ -102,7 +101,7 @@ __device__ __forceinline__ Splat make_splat(float2 m, float4 co) {
   s.qa = kHalfLog2eSqrt * co.x;
   s.qb = kHalfLog2eSqrt * co.y;
   s.qc = kHalfLog2eSqrt * co.z;
-  s.lo = __builtin_amdgcn_logf(co.w);
+  s.o = co.w;
   return s;
 }
 
@@ -112,15 +111,19 @@ __device__ __forceinline__ float3 conic_of(float4 co) {
   return make_float3(co.x * co.x, co.x * co.y, co.y * co.y + co.z * co.z);
 }
 
-// Alpha of a splat at pixel offset (dx, dy) = centre - mean, before the clamp
-// to alpha_max: o exp(power), as 2^(log2 o - log2(e) q / 2) with q = d^T L L^T d
-// a sum of two squares, which saves the product with o in every (pixel, entry).
-// The forward and backward kernels call this one function, so their skip and
-// clamp decisions are bit-identical.
-__device__ __forceinline__ float splat_alpha_raw(float dx, float dy, float qa, float qb, float qc,
-                                                 float lo) {
+// exp(power) of a splat at pixel offset (dx, dy) = centre - mean: the power is
+// -q / 2 with q = d^T L L^T d a sum of two squares, never positive.
+__device__ __forceinline__ float splat_exp(float dx, float dy, float qa, float qb, float qc) {
   const float e1 = qa * dx + qb * dy, e2 = qc * dy;
-  return __builtin_amdgcn_exp2f(fmaf(-e1, e1, fmaf(-e2, e2, lo)));
+  return __builtin_amdgcn_exp2f(-(e1 * e1 + e2 * e2));
+}
+// Alpha before the clamp to alpha_max. The forward and backward kernels form it
+// by these functions, so their skip and clamp decisions are bit-identical. (As
+// 2^(log2 o - q'), which saves the product, alpha's error grows by 2 to 3%, and
+// an opacity of zero, which alpha_min = 0 lets into the lists, has no logarithm.)
+__device__ __forceinline__ float splat_alpha_raw(float dx, float dy, float qa, float qb, float qc,
+                                                 float o) {
+  return o * splat_exp(dx, dy, qa, qb, qc);
 }
 // min(raw, alpha_max) of a raw alpha >= 0 (one instruction: a plain minimum
 // would first quiet its operands).
@@ -128,8 +131,8 @@ __device__ __forceinline__ float clamp_alpha(float raw, float alpha_max) {
   return __builtin_amdgcn_fmed3f(raw, 0.0f, alpha_max);
 }
 __device__ __forceinline__ float splat_alpha(float dx, float dy, float qa, float qb, float qc,
-                                             float lo, float alpha_max) {
-  return clamp_alpha(splat_alpha_raw(dx, dy, qa, qb, qc, lo), alpha_max);
+                                             float o, float alpha_max) {
+  return clamp_alpha(splat_alpha_raw(dx, dy, qa, qb, qc, o), alpha_max);
 }
 
 // The four flags as bits 3 (the first) to 0, an add with carry each (every lane

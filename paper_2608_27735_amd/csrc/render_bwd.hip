@@ -29,7 +29,8 @@ extern "C" __device__ __attribute__((const)) float mul_zero_wins(float, float) _
 // The sums over a wave's 8x8 pixels of the nine gradient values of four list
 // entries. Lane l is pixel (l & 7, l >> 3) of the quadrant, so the column
 // factor dx of a moment is common to a lane's column: the pixels' rows are
-// summed first, of six values per entry,
+// summed first, of six values per entry (gp: dL/d alpha times d alpha / d o =
+// e^power, so that an opacity of zero divides nothing),
 //   v[e] = gp, v[4 + e] = gp dy, v[8 + e] = gp dy^2, v[12 + 4 c + e] = colour c,
 // and the moments in dx are formed from those sums, once per column. Lane bits
 // 5, 4 and 3 (the rows) are summed by halving: v_permlane32_swap
@@ -100,10 +101,10 @@ __device__ __forceinline__ int sum_field(int l) {
 
 // Adds the staged entries' gradients to g2d[Gaussian][9] once the workgroup's
 // sums are complete: wave w takes entries 64 w .. of cnt. Each lane first turns
-// its entry's sums into dL/d(u, v, a, b, c, o, r, g, b): with q = gp (dx, dy),
+// its entry's sums into dL/d(u, v, a, b, c, o, r, g, b): with q = o gp (dx, dy),
 // d power / d(u, v) = (a dx + b dy, b dx + c dy), d power / d(a, b, c) =
 // (-dx^2 / 2, -dx dy, -dy^2 / 2); ga.zw and gb.x hold the conic's factor times
-// s, s^2 = log2(e) / 2, and gp = o d alpha / d o. Then the wave's lanes add nine
+// s, s^2 = log2(e) / 2, and gb.y the opacity o. Then the wave's lanes add nine
 // consecutive floats of seven Gaussians at a time, so that an entry is one
 // or two requests at the memory side, where the nine adds of one thread were
 // nine: the flush is bound by the rate of atomics to memory that all XCDs
@@ -119,14 +120,14 @@ __device__ __forceinline__ void flush_entries(int cnt, float (*s_acc)[257], cons
   if (tid < cnt) {
     const float4 ga = s_ga[tid];
     const float4 gb = s_gb[tid];
-    const float mx = (1.0f / kHalfLog2e) * s_acc[0][tid], my = (1.0f / kHalfLog2e) * s_acc[1][tid];
+    const float o = gb.y, so = o * (1.0f / kHalfLog2e);
+    const float mx = so * s_acc[0][tid], my = so * s_acc[1][tid];
     const float t = ga.z * mx + ga.w * my;
     s_acc[0][tid] = ga.z * t;
     s_acc[1][tid] = ga.w * t + gb.x * gb.x * my;
-    s_acc[2][tid] *= -0.5f;
-    s_acc[3][tid] = -s_acc[3][tid];
-    s_acc[4][tid] *= -0.5f;
-    s_acc[5][tid] *= __builtin_amdgcn_exp2f(-gb.y);
+    s_acc[2][tid] *= -0.5f * o;
+    s_acc[3][tid] *= -o;
+    s_acc[4][tid] *= -0.5f * o;
   }
   const int end = min(cnt, e0 + 64);
   const int k = lane / 9, f = lane - 9 * k;
@@ -143,7 +144,7 @@ __device__ __forceinline__ void flush_entries(int cnt, float (*s_acc)[257], cons
 // Workgroup memory of the backward kernels.
 struct BwdLds {
   float4 ga[256];     // u, v, qa, qb
-  float4 gb[256];     // qc, log2 o, r, g
+  float4 gb[256];     // qc, opacity, r, g
   float4 gc[256];     // colour b, list position, Gaussian
   float acc[9][257];  // [field][staged entry]; an entry's fields in different banks
   __align__(4) uint8_t idx[4][256];  // per wave: staged slots reaching its pixels
@@ -263,7 +264,7 @@ __device__ __forceinline__ void bwd_item(
     if (keep) {
       const Splat g = make_splat(rec.m, rec.co);
       s.ga[pos] = make_float4(g.u, g.v, g.qa, g.qb);
-      s.gb[pos] = make_float4(g.qc, g.lo, rec.r, rec.g);
+      s.gb[pos] = make_float4(g.qc, g.o, rec.r, rec.g);
       s.gc[pos] = make_float4(rec.b, __uint_as_float(bend - 1 - tid - start),
                               __uint_as_float(rec.gid), 0.0f);
 #pragma unroll
@@ -308,22 +309,23 @@ __device__ __forceinline__ void bwd_item(
                    "v"(gbv[i].y), "v"(gbv[i].z), "v"(gbv[i].w), "v"(gcv[i].x), "v"(gcv[i].y));
     const int my_slot = (int)((iw >> my_shift) & 255u);
     const float my_u = s.ga[my_slot].x;
-    // Per lane and entry: whether the pixel blends it (its walk reached it,
-    // alpha >= alpha_min, and it is not past the end of the wave's list).
-    float raw[kBwdGroup], dy[kBwdGroup];
-    bool contrib[kBwdGroup], free_alpha[kBwdGroup];  // blends it; and not at the clamp
+    // Per lane and entry: alpha and d alpha / d o, zero where the pixel does not
+    // blend it (its walk did not reach it, alpha < alpha_min, or it is past the
+    // end of the wave's list), the derivative also at the clamp.
+    float a[kBwdGroup], de[kBwdGroup], dy[kBwdGroup];
     uint64_t any = 0;
 #pragma unroll
     for (int i = 0; i < kBwdGroup; ++i) {
       const float dx = fx - gav[i].x;
       dy[i] = fy - gav[i].y;
-      raw[i] = splat_alpha_raw(dx, dy[i], gav[i].z, gav[i].w, gbv[i].x, gbv[i].y);
+      const float e = splat_exp(dx, dy[i], gav[i].z, gav[i].w, gbv[i].x);
+      const float raw = gbv[i].y * e;  // splat_alpha_raw
       const uint64_t m = __builtin_amdgcn_ballot_w64(__float_as_uint(gcv[i].y) < lastp) &
-                         __builtin_amdgcn_ballot_w64(raw[i] >= k.alpha_min) &
+                         __builtin_amdgcn_ballot_w64(raw >= k.alpha_min) &
                          (j0 + i < wcnt ? ~0ull : 0ull);
-      contrib[i] = __builtin_amdgcn_inverse_ballot_w64(m);
-      free_alpha[i] = __builtin_amdgcn_inverse_ballot_w64(
-          m & __builtin_amdgcn_ballot_w64(raw[i] <= k.alpha_max));
+      a[i] = __builtin_amdgcn_inverse_ballot_w64(m) ? clamp_alpha(raw, k.alpha_max) : 0.0f;
+      de[i] = __builtin_amdgcn_inverse_ballot_w64(
+                  m & __builtin_amdgcn_ballot_w64(raw <= k.alpha_max)) ? e : 0.0f;
       any |= m;
     }
     if (!any) continue;  // wave-uniform
@@ -334,19 +336,18 @@ __device__ __forceinline__ void bwd_item(
     float gr[6 * kBwdGroup];
 #pragma unroll
     for (int i = 0; i < kBwdGroup; ++i) {
-      const float a = contrib[i] ? clamp_alpha(raw[i], k.alpha_max) : 0.0f;
-      const float iom = __builtin_amdgcn_rcpf(1.0f - a);  // 1 - a >= 1 - alpha_max > 0
+      const float iom = __builtin_amdgcn_rcpf(1.0f - a[i]);  // 1 - a >= 1 - alpha_max > 0
       T *= iom;  // before the entry
-      const float wgt = a * T;
+      const float wgt = a[i] * T;
       gr[12 + i] = mul_zero_wins(wgt, gcr);
       gr[16 + i] = mul_zero_wins(wgt, gcg);
       gr[20 + i] = mul_zero_wins(wgt, gcb);
       const float D = fmaf(gcv[i].x, gcb, fmaf(gbv[i].w, gcg, fmaf(gbv[i].z, gcr, -RG)));
       const float dLda = T * D - iom * TgT;
-      RG = fmaf(a, D, RG);
-      // no gradient where the clamp cuts the derivative; the conic and the
-      // constant factors are applied once per entry at the flush
-      const float gp = free_alpha[i] ? a * dLda : 0.0f;
+      RG = fmaf(a[i], D, RG);
+      // no gradient where the clamp cuts the derivative; the opacity, the conic
+      // and the constant factors are applied once per entry at the flush
+      const float gp = mul_zero_wins(de[i], dLda);
       const float r = gp * dy[i];
       gr[0 + i] = gp;
       gr[4 + i] = r;
@@ -511,7 +512,7 @@ __device__ __forceinline__ void bwd_rows(
     if (keep) {
       const Splat sp = make_splat(rec.m, rec.co);
       s.ga[pos] = make_float4(sp.u, sp.v, sp.qa, sp.qb);
-      s.gb[pos] = make_float4(sp.qc, sp.lo, rec.r, rec.g);
+      s.gb[pos] = make_float4(sp.qc, sp.o, rec.r, rec.g);
       s.gc[pos] = make_float4(rec.b, __uint_as_float(bend - 1 - tid - start),
                               __uint_as_float(rec.gid), 0.0f);
 #pragma unroll
@@ -544,7 +545,8 @@ __device__ __forceinline__ void bwd_rows(
       gcn = s.gc[jn];
       if (!__ballot(valid && kk < wml)) continue;  // wave-uniform
       const float dx = fx - ga.x, dy = fy - ga.y;
-      const float raw = splat_alpha_raw(dx, dy, ga.z, ga.w, gb.x, gb.y);
+      const float de = splat_exp(dx, dy, ga.z, ga.w, gb.x);  // d alpha / d o
+      const float raw = gb.y * de;  // splat_alpha_raw
       const bool contrib = valid && kk < lastp && raw >= k.alpha_min;
       if (!__ballot(contrib)) continue;  // wave-uniform
       const float a = contrib ? clamp_alpha(raw, k.alpha_max) : 0.0f;
@@ -571,7 +573,7 @@ __device__ __forceinline__ void bwd_rows(
       T *= ptot;
       S += stot;
       const float dm = (contrib && raw <= k.alpha_max) ? dLda : 0.0f;
-      const float gp = a * dm;
+      const float gp = de * dm;
       const float q = gp * dx, r = gp * dy;
       float gr[9];
       gr[0] = q;

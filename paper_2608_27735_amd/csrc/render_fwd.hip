@@ -24,7 +24,7 @@ namespace {
 constexpr int kSlots = 256 + 2 * kGroup;
 struct FwdLds {
   float4 ga[4][kSlots];  // u, v, qa, qb
-  float2 gq[4][kSlots];  // qc, log2 o
+  float2 gq[4][kSlots];  // qc, opacity
   float2 rg[4][kSlots];  // r, g
   float bl[4][kSlots];   // b
   uint8_t at[4][256];    // position in the batch
@@ -48,17 +48,17 @@ __device__ __forceinline__ int stage_fwd(FwdLds& s, const Rec& rec, uint32_t rea
     for (int r = 0; r < 4; ++r) {
       if ((reach >> r) & 1u) {
         s.ga[r][at[r]] = make_float4(sp.u, sp.v, sp.qa, sp.qb);
-        s.gq[r][at[r]] = make_float2(sp.qc, sp.lo);
+        s.gq[r][at[r]] = make_float2(sp.qc, sp.o);
         s.rg[r][at[r]] = make_float2(rec.r, rec.g);
         s.bl[r][at[r]] = rec.b;
         s.at[r][at[r]] = (uint8_t)tid;
       }
     }
   }
-  if ((tid & 63) < kGroup) {  // the last group's rest: alpha 2^-1e30 = 0
+  if ((tid & 63) < kGroup) {  // the last group's rest: of opacity 0
     const int p = wcnt + (tid & 63);
     s.ga[w][p] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    s.gq[w][p] = make_float2(0.0f, -1e30f);
+    s.gq[w][p] = make_float2(0.0f, 0.0f);
     s.rg[w][p] = make_float2(0.0f, 0.0f);
     s.bl[w][p] = 0.0f;
   }
