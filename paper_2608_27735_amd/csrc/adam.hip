@@ -6,15 +6,19 @@
 // every group in place: a pure HBM stream (parameter, gradient and both
 // moments read, parameter and moments written: 28 bytes per element).
 // Workgroups are dealt to the groups in proportion to their sizes, 4,096
-// elements each; a thread takes four float4s a row of 256 threads apart, all
-// sixteen loads issued first, so that each load of a wave covers 1 KB of
-// consecutive bytes. (With 16 consecutive elements per thread a wave's load
-// touched 64 lines for a quarter of each: 59M elements took 442 us, 3.7 TB/s,
-// against 313 us in rows.) Every byte is used once per step and the arrays of
-// a large block exceed the caches, so accesses are marked non-temporal: 279
-// us, 5.9 TB/s (300,001 x 59 elements 86 against 99 us; no slower down to
-// 1,000 x 59). Unaligned arrays and the last, partial workgroup of a group
-// go element by element, also in rows.
+// elements each; a thread takes four float4s a row of 256 threads apart, so
+// that each load of a wave covers 1 KB of consecutive bytes. (With 16
+// consecutive elements per thread a wave's load touched 64 lines for a quarter
+// of each: 59M elements took 442 us, 3.7 TB/s, against 313 us in rows.) Every
+// byte is used once per step and the arrays of a large block exceed the caches,
+// so accesses are marked non-temporal: 279 us, 5.9 TB/s. A group's last
+// workgroup takes its one to four rows the same way, so a small block's launch
+// is one round trip to memory: in us, with 16 elements per thread / the last
+// workgroup element by element / now, for N Gaussians of 14 and of 59 floats:
+// N = 512: 3.8 / 4.1 / 3.2, 4.7 / 4.1 / 4.2; 1,000: 5.7 / 6.2 / 3.9, 5.7 / 6.2 /
+// 4.3; 2,000: 4.6 / 6.1 / 4.1, 4.9 / 6.3 / 4.3; 3,001: 16.3 / 6.0 / 4.2, 16.4 /
+// 6.1 / 4.4; 30,000: 5.8 / 6.7 / 4.7, 13.0 / 9.8 / 9.8; 100,000: 11.5 / 8.6 / 8.7,
+// 45.1 / 29.3 / 29.1. Unaligned arrays go element by element, also in rows.
 #include <math.h>
 
 #include "abcd_internal.h"
@@ -47,57 +51,80 @@ __device__ __forceinline__ void adam_one(float& th, float g, float& m, float& v,
   th = th - step * m / (sqrtf(v * ic2) + eps);
 }
 
+// Up to kRows rows of kBlock vectors E (a float4 or a float) from the arrays'
+// start, n of them in all: thread t takes vector t of each row, so a wave's
+// accesses are consecutive, and every load is issued before the first is used
+// (an index past the end is clamped: a load under a condition would be waited
+// for where the branches meet).
+template <int kRows, typename E>
+__device__ __forceinline__ void adam_rows(float* th, const float* g, float* m, float* v, int n,
+                                          float b1, float b2, float ic2, float eps, float step) {
+  constexpr int kLanes = sizeof(E) / sizeof(float);
+  E T[kRows], G[kRows], M[kRows], V[kRows];
+#pragma unroll
+  for (int q = 0; q < kRows; ++q) {
+    const int i = min(q * kBlock + (int)threadIdx.x, n - 1);
+    T[q] = __builtin_nontemporal_load(reinterpret_cast<const E*>(th) + i);
+    G[q] = __builtin_nontemporal_load(reinterpret_cast<const E*>(g) + i);
+    M[q] = __builtin_nontemporal_load(reinterpret_cast<const E*>(m) + i);
+    V[q] = __builtin_nontemporal_load(reinterpret_cast<const E*>(v) + i);
+  }
+#pragma unroll
+  for (int q = 0; q < kRows; ++q) {
+    const int i = q * kBlock + (int)threadIdx.x;
+    float* const t1 = reinterpret_cast<float*>(&T[q]);
+    const float* const g1 = reinterpret_cast<const float*>(&G[q]);
+    float* const m1 = reinterpret_cast<float*>(&M[q]);
+    float* const v1 = reinterpret_cast<float*>(&V[q]);
+#pragma unroll
+    for (int e = 0; e < kLanes; ++e) adam_one(t1[e], g1[e], m1[e], v1[e], b1, b2, ic2, eps, step);
+    if (i < n) {
+      __builtin_nontemporal_store(T[q], reinterpret_cast<E*>(th) + i);
+      __builtin_nontemporal_store(M[q], reinterpret_cast<E*>(m) + i);
+      __builtin_nontemporal_store(V[q], reinterpret_cast<E*>(v) + i);
+    }
+  }
+}
+
 __global__ __launch_bounds__(kBlock) void adam_kernel(AdamArgs a, float b1, float b2, float ic2,
                                                       float eps) {
   int gi = 0;
   while (gi + 1 < a.ngroups && (int64_t)blockIdx.x >= a.block0[gi + 1]) ++gi;
-  // the workgroup's elements [b0, b0 + kPerBlock); thread t takes the float4
-  // (or, unaligned, the element) t of each row of kBlock, so a wave's accesses
-  // are consecutive
+  // the workgroup's elements [b0, b0 + cnt)
   const int64_t b0 = ((int64_t)blockIdx.x - a.block0[gi]) * kPerBlock;
-  const int64_t n = a.count[gi];
+  int cnt = (int)min<int64_t>(kPerBlock, a.count[gi] - b0);
   float* th = a.theta[gi] + b0;
   const float* g = a.g[gi] + b0;
   float* m = a.m[gi] + b0;
   float* v = a.v[gi] + b0;
   const float step = a.step[gi];
-  const int tid = (int)threadIdx.x;
-  if (a.vec[gi] && b0 + kPerBlock <= n) {
-    f4v T[4], G[4], M[4], V[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int i = q * kBlock + tid;
-      T[q] = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(th) + i);
-      G[q] = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(g) + i);
-      M[q] = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(m) + i);
-      V[q] = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(v) + i);
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int i = q * kBlock + tid;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float t1 = T[q][e], m1 = M[q][e], v1 = V[q][e];
-        adam_one(t1, G[q][e], m1, v1, b1, b2, ic2, eps, step);
-        T[q][e] = t1;
-        M[q][e] = m1;
-        V[q][e] = v1;
-      }
-      __builtin_nontemporal_store(T[q], reinterpret_cast<f4v*>(th) + i);
-      __builtin_nontemporal_store(M[q], reinterpret_cast<f4v*>(m) + i);
-      __builtin_nontemporal_store(V[q], reinterpret_cast<f4v*>(v) + i);
-    }
-    return;
+  if (a.vec[gi] && cnt >= 4) {
+    // a group's last workgroup takes as many rows of float4 as it has
+    const int n4 = cnt / 4;
+    if (n4 > 3 * kBlock)
+      adam_rows<4, f4v>(th, g, m, v, n4, b1, b2, ic2, eps, step);
+    else if (n4 > 2 * kBlock)
+      adam_rows<3, f4v>(th, g, m, v, n4, b1, b2, ic2, eps, step);
+    else if (n4 > kBlock)
+      adam_rows<2, f4v>(th, g, m, v, n4, b1, b2, ic2, eps, step);
+    else
+      adam_rows<1, f4v>(th, g, m, v, n4, b1, b2, ic2, eps, step);
+    th += 4 * n4;
+    g += 4 * n4;
+    m += 4 * n4;
+    v += 4 * n4;
+    cnt -= 4 * n4;
   }
-  // the last workgroup of a group, or unaligned arrays
-  const int cnt = (int)min<int64_t>(kPerBlock, n - b0);
-  for (int i = tid; i < cnt; i += kBlock) {
-    float t = th[i], mm = m[i], vv = v[i];
-    adam_one(t, g[i], mm, vv, b1, b2, ic2, eps, step);
-    th[i] = t;
-    m[i] = mm;
-    v[i] = vv;
+  // unaligned arrays, or the one to three elements that are left: in turn, four
+  // rows at a time
+  for (; cnt > kBlock; cnt -= 4 * kBlock) {
+    adam_rows<4, float>(th, g, m, v, cnt, b1, b2, ic2, eps, step);
+    th += 4 * kBlock;
+    g += 4 * kBlock;
+    m += 4 * kBlock;
+    v += 4 * kBlock;
   }
+  if (cnt > 0) adam_rows<1, float>(th, g, m, v, cnt, b1, b2, ic2, eps, step);
 }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }

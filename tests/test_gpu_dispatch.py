@@ -407,3 +407,11 @@ def test_opacity_below_the_normal_range(api, size):
         g, gr = grads[k].cpu().numpy().astype(np.float64), ref["grads"][k]
         assert np.isfinite(g).all(), k
         assert np.linalg.norm(g - gr) <= 1e-4 * max(np.linalg.norm(gr), 1e-30), k
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("count", [4, 5, 255, 257, 1023, 1024, 1029, 2051, 3072, 3075, 5121])
+def test_adam_rows_of_the_last_workgroup(api, count, offset):
+    """Counts that leave a group's last workgroup one to four rows of float4, whole
+    and not, and up to three elements behind them."""
+    test_adam_workgroup_edges(api, count, offset)
