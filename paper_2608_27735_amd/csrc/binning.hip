@@ -1313,8 +1313,7 @@ __global__ __launch_bounds__(kSmallThreads) void bin_small_sort_kernel(
     unsigned long long capacity, uint32_t* __restrict__ sorted_g, uint32_t* __restrict__ sorted_rect,
     uint32_t* __restrict__ tile_off, uint32_t* __restrict__ tile_ranges,
     uint32_t* __restrict__ tile_order, WsHeader* __restrict__ hdr) {
-  extern __shared__ __align__(16) unsigned char small_lds[];
-  SmallLds<kItems>& s = *reinterpret_cast<SmallLds<kItems>*>(small_lds);
+  __shared__ SmallLds<kItems> s;
   constexpr int kPerWave = 64 * kItems;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int ntiles = geo.ntx * geo.nty;
@@ -1616,8 +1615,15 @@ __global__ __launch_bounds__(256) void bin_count_kernel(
   if (threadIdx.x == 0 && s_m) atomicAdd(m_out, s_m);
 }
 
-int32_t set_max_lds(const void* fn, size_t bytes) {
+// Raises the limit of fn's dynamic workgroup memory on the current device, once
+// for each (done: a bit per device; those past 64 are set on every call).
+int32_t set_max_lds(const void* fn, size_t bytes, std::atomic<uint64_t>& done) {
+  int dev = 0;
+  ABCD_HIP(hipGetDevice(&dev));
+  const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0ull;
+  if (done.load(std::memory_order_acquire) & bit) return ABCD_OK;
   ABCD_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+  done.fetch_or(bit, std::memory_order_release);
   return ABCD_OK;
 }
 
@@ -1646,17 +1652,9 @@ int32_t launch_bin_sort(int width, int height, int64_t n, const float* means2d, 
   if (small_path(n, geo)) {
     const unsigned long long cap_s = (unsigned long long)std::max<int64_t>(capacity, 0);
 #define ABCD_SMALL(kItems)                                                                       \
-  do {                                                                                            \
-    static std::atomic<bool> lds_set{false};                                                      \
-    if (!lds_set.load(std::memory_order_acquire)) {                                               \
-      TRY_STATUS(set_max_lds((const void*)bin_small_sort_kernel<kItems>, sizeof(SmallLds<kItems>))); \
-      lds_set.store(true, std::memory_order_release);                                             \
-    }                                                                                             \
-    ABCD_LAUNCH("bin_small_sort", bin_small_sort_kernel<kItems>, 1, kSmallThreads,                \
-                sizeof(SmallLds<kItems>), stream, (int)n, depth, tiles_touched, means2d, extent,  \
-                geo, cap_s, u32(L.keys_a), u32(L.keys_b), u32(L.tile_off), tile_ranges,           \
-                tile_order, hdr);                                                                 \
-  } while (0)
+  ABCD_LAUNCH("bin_small_sort", bin_small_sort_kernel<kItems>, 1, kSmallThreads, 0, stream,       \
+              (int)n, depth, tiles_touched, means2d, extent, geo, cap_s, u32(L.keys_a),           \
+              u32(L.keys_b), u32(L.tile_off), tile_ranges, tile_order, hdr)
     if (n <= 1 * kSmallThreads)
       ABCD_SMALL(1);
     else if (n <= 2 * kSmallThreads)
@@ -1702,18 +1700,13 @@ int32_t launch_bin_sort(int width, int height, int64_t n, const float* means2d, 
                 kBlock, 0, stream, reinterpret_cast<uint4*>(ws + L.hdr), words, n, depth,
                 tiles_touched, parts, range);
   }
-  static bool attrs_set = false;
-  if (!attrs_set) {
-    // depth_keys keeps 4 words and level 1 5 words per block of any frame of
-    // at most ABCD_MAX_TILES tiles (at most ABCD_MAX_TILES / 8 blocks)
-    int32_t st = set_max_lds((const void*)depth_keys_kernel,
-                             4 * sizeof(uint32_t) * (ABCD_MAX_TILES / kBlk + 1));
-    if (st != ABCD_OK) return st;
-    st = set_max_lds((const void*)l1_place_kernel,
-                     5 * sizeof(uint32_t) * (ABCD_MAX_TILES / kBlk + 1));
-    if (st != ABCD_OK) return st;
-    attrs_set = true;
-  }
+  // depth_keys keeps 4 words and level 1 5 words per block of any frame of at
+  // most ABCD_MAX_TILES tiles (at most ABCD_MAX_TILES / 8 blocks)
+  static std::atomic<uint64_t> keys_set{0}, l1_set{0};
+  TRY_STATUS(set_max_lds((const void*)depth_keys_kernel,
+                         4 * sizeof(uint32_t) * (ABCD_MAX_TILES / kBlk + 1), keys_set));
+  TRY_STATUS(set_max_lds((const void*)l1_place_kernel,
+                         5 * sizeof(uint32_t) * (ABCD_MAX_TILES / kBlk + 1), l1_set));
   uint32_t* bcopy = u32(L.bcopy);
   unsigned long long* mcopy = reinterpret_cast<unsigned long long*>(ws + L.mcopy);
   ABCD_LAUNCH("depth_keys", depth_keys_kernel, (n + kDkTile - 1) / kDkTile, kBlock,

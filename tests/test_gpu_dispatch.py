@@ -415,3 +415,24 @@ def test_adam_rows_of_the_last_workgroup(api, count, offset):
     """Counts that leave a group's last workgroup one to four rows of float4, whole
     and not, and up to three elements behind them."""
     test_adam_workgroup_edges(api, count, offset)
+
+
+def test_binning_workgroup_memory_on_each_device(api):
+    """The largest workgroup memory of each binning path on every device of the
+    process, one after the other: the limit of dynamic memory is each device's own."""
+    from paper_2608_27735_amd.camera import RasterParams, look_at
+    for n, size in ((8192, (203, 117)), (9000, (203, 117)), (9000, (16, 16 * 32768))):
+        r = S.rng(1400 + n)
+        cam = look_at((0.2, -3.0, 0.9), (0, 0, 0), *size)
+        sc = S.gaussians(r, r.uniform(-1.5, 1.5, (n, 3)), 0, np.log(0.02), 0.6)
+        prm = RasterParams(sh_degree=0)
+        pb = O.project_bin(cam, prm, sc["means"], sc["log_scales"], sc["quats"], sc["opacity_logits"])
+        keys, values, ranges = O.bin(cam.width, cam.height, pb["depth"], pb["rect"], pb["tiles_touched"])
+        for k in range(torch.cuda.device_count()):
+            say("workgroup memory", k, n, size)
+            with torch.cuda.device(k):
+                proj = api.project(cam, prm, **{a: torch.from_numpy(v).to(f"cuda:{k}") for a, v in sc.items()})
+                b = api.bin_sort(cam.width, cam.height, proj)
+                torch.cuda.synchronize()
+                assert np.array_equal(b["values"][:len(values)].cpu().numpy().view(np.uint32), values)
+                assert np.array_equal(b["tile_ranges"].cpu().numpy().view(np.uint32), ranges)
