@@ -1243,18 +1243,25 @@ __device__ __forceinline__ uint32_t pack_rect8(int x0, int y0, int x1, int y1) {
   return (uint32_t)x0 | ((uint32_t)x1 << 8) | ((uint32_t)y0 << 16) | ((uint32_t)y1 << 24);
 }
 
+// Inclusive prefix sum over the wave: within rows of 16 lanes, then each row's
+// total into the rows after it.
+__device__ __forceinline__ int wave_prefix_i32(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);   // row shift right 1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);   // 2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);   // 4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);   // 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // broadcast 15
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // broadcast 31
+  return v;
+}
+
 // Exclusive scan over the threads of a workgroup of kSmallThreads: each wave
-// scans its 64 values with shuffles, one barrier publishes the wave totals
+// scans its 64 values, one barrier publishes the wave totals
 // (s: kSmallWaves words of LDS), and each thread adds the totals of the waves
 // before its own. Returns the exclusive prefix and the total in *tot.
 __device__ __forceinline__ uint32_t scan_small(uint32_t v, uint32_t* s, uint32_t* tot) {
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  uint32_t incl = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t y = (uint32_t)__shfl_up((int)incl, d, 64);
-    if (lane >= d) incl += y;
-  }
+  const uint32_t incl = (uint32_t)wave_prefix_i32((int)v);
   if (lane == 63) s[w] = incl;
   __syncthreads();
   uint32_t before = 0, all = 0;
@@ -1267,17 +1274,6 @@ __device__ __forceinline__ uint32_t scan_small(uint32_t v, uint32_t* s, uint32_t
   *tot = all;
   __syncthreads();
   return before + incl - v;
-}
-
-// Inclusive prefix sum over the wave.
-__device__ __forceinline__ int wave_prefix_i32(int v) {
-  const int lane = __lane_id();
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int y = __shfl_up(v, d, 64);
-    if (lane >= d) v += y;
-  }
-  return v;
 }
 
 // Workgroup memory of the one-workgroup sort of up to 1,024 kItems Gaussians.
@@ -1365,11 +1361,8 @@ __global__ __launch_bounds__(kSmallThreads) void bin_small_sort_kernel(
   }
   const unsigned long long wm = wave_sum_u64(m);
   if (lane == 0 && wm) atomicAdd(&s.m, wm);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    lo = min(lo, (uint32_t)__shfl_xor((int)lo, off, 64));
-    hi = max(hi, (uint32_t)__shfl_xor((int)hi, off, 64));
-  }
+  lo = wave_min_u32(lo);
+  hi = ~wave_min_u32(~hi);
   if (lane == 0) {
     atomicMin(&s.lo, lo);
     atomicMax(&s.hi, hi);
@@ -1444,17 +1437,23 @@ __global__ __launch_bounds__(kSmallThreads) void bin_small_sort_kernel(
     __syncthreads();
     // digit d: total over the waves, exclusive base over the digits, then the
     // waves' offsets in place
-    uint32_t tot_d = 0;
-    if (tid < 256)
-      for (int v = 0; v < nw; ++v) tot_d += s.cnt[v][tid];
+    uint32_t tot_d = 0, c[kSmallWaves];
+    if (tid < 256) {
+#pragma unroll
+      for (int v = 0; v < kSmallWaves; ++v) {
+        c[v] = v < nw ? s.cnt[v][tid] : 0u;
+        tot_d += c[v];
+      }
+    }
     uint32_t total;
     uint32_t base = scan_small(tid < 256 ? tot_d : 0u, s.scan, &total);
-    if (tid < 256)
-      for (int v = 0; v < nw; ++v) {
-        const uint32_t c = s.cnt[v][tid];
-        s.cnt[v][tid] = (uint16_t)base;
-        base += c;
+    if (tid < 256) {
+#pragma unroll
+      for (int v = 0; v < kSmallWaves; ++v) {
+        if (v < nw) s.cnt[v][tid] = (uint16_t)base;
+        base += c[v];
       }
+    }
     __syncthreads();
 #pragma unroll
     for (int it = 0; it < kItems; ++it) {
@@ -1504,35 +1503,48 @@ __global__ __launch_bounds__(kSmallThreads) void bin_small_sort_kernel(
 
 // One workgroup per tile: the sorted Gaussians whose rectangle covers the
 // tile, in sorted order. Wave w takes a quarter of the positions, counts its
-// hits, and stores them once the counts of the waves before it are known: the
-// rectangles are read twice (from cache), 8 x 64 at a time, with one barrier.
+// hits, and stores them once the counts of the waves before it are known: one
+// barrier. Up to 2,048 Gaussians (kOnce) a wave holds its quarter's rectangles
+// and indices in registers, 8 x 64 positions, all loads in flight at once; above,
+// it reads them 8 x 64 at a time, the rectangles again (from cache) to store.
+constexpr int kAhead = 8;
+constexpr int kOnceN = 4 * 64 * kAhead;
+
+template <bool kOnce>
 __global__ __launch_bounds__(256) void bin_small_collect_kernel(
     int n, const float* __restrict__ depth, Geo geo, const uint32_t* __restrict__ sorted_g,
     const uint32_t* __restrict__ sorted_rect, const uint32_t* __restrict__ tile_off,
     const WsHeader* __restrict__ hdr, uint32_t* __restrict__ values_sorted,
     unsigned long long* __restrict__ keys_sorted) {
   __shared__ uint32_t s_w[4];
-  if (hdr->overflow) return;
   const int t = blockIdx.x, tx = t % geo.ntx, ty = t / geo.ntx;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const uint64_t lt = lanemask_lt();
   const int quarter = ((n + 255) / 256) * 64;  // positions per wave
   const int j0 = w * quarter, j1 = min(n, j0 + quarter);
-  const uint32_t off = tile_off[t];
+  const uint32_t off = tile_off[t], overflow = hdr->overflow;
   auto covers = [&](uint32_t r) {
     const int x0 = r & 255, x1 = (r >> 8) & 255, y0 = (r >> 16) & 255, y1 = r >> 24;
     return x0 <= tx && tx <= x1 && y0 <= ty && ty <= y1;
   };
-  constexpr int kAhead = 8;
   constexpr uint32_t kEmpty = 1u;  // x0 = 1 > x1 = 0
-  uint32_t count = 0;
-  for (int j = j0; j < j1; j += 64 * kAhead) {
-    uint32_t r[kAhead];
+  uint32_t r[kAhead], g[kAhead];
+  auto load = [&](int j, bool indices) {
 #pragma unroll
     for (int a = 0; a < kAhead; ++a) {
-      const int i = j + 64 * a + lane;
-      r[a] = i < j1 ? sorted_rect[i] : kEmpty;
+      const int i = min(j + 64 * a + lane, n - 1);  // unconditional loads
+      r[a] = sorted_rect[i];
+      if (indices) g[a] = sorted_g[i];
     }
+#pragma unroll
+    for (int a = 0; a < kAhead; ++a)
+      if (j + 64 * a + lane >= j1) r[a] = kEmpty;
+  };
+  uint32_t count = 0;
+  if (kOnce) load(j0, true);
+  if (overflow) return;  // uniform
+  for (int j = j0; j < (kOnce ? j0 + 1 : j1); j += 64 * kAhead) {
+    if (!kOnce) load(j, false);
 #pragma unroll
     for (int a = 0; a < kAhead; ++a) count += (uint32_t)__popcll(__ballot(covers(r[a])));
   }
@@ -1541,14 +1553,8 @@ __global__ __launch_bounds__(256) void bin_small_collect_kernel(
   uint32_t run = off;
 #pragma unroll
   for (int v = 0; v < 3; ++v) run += v < w ? s_w[v] : 0u;
-  for (int j = j0; j < j1; j += 64 * kAhead) {
-    uint32_t r[kAhead], g[kAhead];
-#pragma unroll
-    for (int a = 0; a < kAhead; ++a) {
-      const int i = j + 64 * a + lane;
-      r[a] = i < j1 ? sorted_rect[i] : kEmpty;
-      g[a] = i < j1 ? sorted_g[i] : 0u;
-    }
+  for (int j = j0; j < (kOnce ? j0 + 1 : j1); j += 64 * kAhead) {
+    if (!kOnce) load(j, true);
 #pragma unroll
     for (int a = 0; a < kAhead; ++a) {
       const bool hit = covers(r[a]);
@@ -1664,9 +1670,15 @@ int32_t launch_bin_sort(int width, int height, int64_t n, const float* means2d, 
     else
       ABCD_SMALL(8);
 #undef ABCD_SMALL
-    ABCD_LAUNCH("bin_small_collect", bin_small_collect_kernel, ntiles, kBlock, 0, stream, (int)n,
-                depth, geo, u32(L.keys_a), u32(L.keys_b), u32(L.tile_off), hdr, values_sorted,
-                reinterpret_cast<unsigned long long*>(keys_sorted));
+#define ABCD_COLLECT(kOnce)                                                                      \
+  ABCD_LAUNCH("bin_small_collect", bin_small_collect_kernel<kOnce>, ntiles, kBlock, 0, stream,    \
+              (int)n, depth, geo, u32(L.keys_a), u32(L.keys_b), u32(L.tile_off), hdr,             \
+              values_sorted, reinterpret_cast<unsigned long long*>(keys_sorted))
+    if (n <= kOnceN)
+      ABCD_COLLECT(true);
+    else
+      ABCD_COLLECT(false);
+#undef ABCD_COLLECT
     ABCD_HIP(hipGetLastError());
     return ABCD_OK;
   }

@@ -436,3 +436,11 @@ def test_binning_workgroup_memory_on_each_device(api):
                 torch.cuda.synchronize()
                 assert np.array_equal(b["values"][:len(values)].cpu().numpy().view(np.uint32), values)
                 assert np.array_equal(b["tile_ranges"].cpu().numpy().view(np.uint32), ranges)
+
+
+@pytest.mark.parametrize("size", [(203, 117), (1280, 400)])
+@pytest.mark.parametrize("n", [64, 255, 257, 513, 2047, 2048])
+def test_binning_collect_of_one_round(api, n, size):
+    """Blocks of up to 2,048 Gaussians, whose rectangles the collection holds in
+    registers: quarters of one to eight rounds of 64 positions, whole and not."""
+    test_binning_small_block_sizes(api, n, size)
