@@ -110,11 +110,12 @@ def check(status):
 
 
 def _fill(dst, values):
-    """The first len(dst) numbers of values into a ctypes array. A NumPy array of
-    that size goes as a whole: element by element the three arrays of a camera
-    took 6 of the 13 us that a call of a kernel spends on the host."""
-    if type(values) is np.ndarray and values.size == len(dst):
-        dst[:] = values.ravel().tolist()
+    """The first len(dst) numbers of values into a ctypes array. A flat NumPy array
+    of that many real numbers goes as a whole: element by element the three arrays
+    of a camera took 6 of the 13 us that a call of a kernel spends on the host."""
+    if (type(values) is np.ndarray and values.ndim == 1 and values.size == len(dst)
+            and values.dtype.kind in "fiu"):
+        dst[:] = values.tolist()
         return
     for i in range(len(dst)):
         dst[i] = float(values[i])
@@ -125,7 +126,9 @@ def camera_struct(cam):
     c.width, c.height = int(cam.width), int(cam.height)
     c.fx, c.fy, c.cx, c.cy = float(cam.fx), float(cam.fy), float(cam.cx), float(cam.cy)
     R = cam.R
-    if (type(R) is not np.ndarray or R.size != 9) and hasattr(R[0], "__len__"):
+    if type(R) is np.ndarray and R.ndim == 2 and R.size == 9:
+        R = R.ravel()
+    elif hasattr(R[0], "__len__"):
         R = [float(x) for row in R for x in row]
     _fill(c.R, R)
     _fill(c.t, cam.t)
