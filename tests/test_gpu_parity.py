@@ -25,7 +25,7 @@ pytestmark = pytest.mark.gpu
 FWD_TOL = 1e-5
 GRAD_TOL = 1e-4
 KNIFE = 1e-4
-# frames of at most this many tiles render, when not split, with four
+# the forward of frames of at most this many tiles takes, when not split, four
 # workgroups per tile (one pixel row per wave, four list entries per step)
 ROWS_TILES = 256
 
@@ -84,9 +84,10 @@ def cases():
     sc4 = S.gaussians(rs, rs.uniform((-0.8, -0.8, -0.6), (0.8, 0.8, 0.6), (6000, 3)), 1,
                       math.log(0.012), 0.4)
     out.append(("small-splats-100x75", cam, RasterParams(sh_degree=1), sc4))
-    # small active blocks take the two-launch binning (at most 2,048 Gaussians,
-    # 2,048 tiles): a ragged frame, and the largest block it takes next to one
-    # Gaussian more (the general path)
+    # small active blocks take the two-launch binning (at most 8,192 Gaussians,
+    # 2,048 tiles): a ragged frame, both sides of the size from which its
+    # collection reads twice, and the largest block it takes next to one Gaussian
+    # more (the general path)
     rk = S.rng(24)
     cam = look_at((0.2, -3.0, 0.9), (0, 0, 0), 203, 117)
     sc5 = S.gaussians(rk, rk.uniform(-1, 1, (1500, 3)), 2, math.log(0.05), 0.6)
@@ -94,15 +95,20 @@ def cases():
     ring_n = {k: v[:2048] for k, v in r.scene.items()}
     out.append(("small-path-2048-cam1", r.cams[1], r.params, ring_n))
     # frames on both sides of the tile count up to which the blend kernels
-    # give each tile four workgroups (256 = 16 x 16 tiles; 17 x 16 = 272)
+    # give each tile four workgroups (256 = 16 x 16 tiles; 17 x 16 = 272, where
+    # the backward still does so for lists of 128 entries or more), and past the
+    # one up to which the unsplit backward goes without a schedule (1,024)
     rb = S.rng(25)
     scb = S.gaussians(rb, rb.uniform(-1, 1, (2500, 3)), 1, math.log(0.04), 0.5)
     out.append(("rows-256-tiles-256x256", look_at((0.1, -3.0, 0.8), (0, 0, 0), 256, 256),
                 RasterParams(sh_degree=1), scb))
     out.append(("general-272-tiles-272x256", look_at((0.1, -3.0, 0.8), (0, 0, 0), 272, 256),
                 RasterParams(sh_degree=1), scb))
-    out.append(("general-path-2049-cam1", r.cams[1], r.params,
-                {k: v[:2049] for k, v in r.scene.items()}))
+    out.append(("general-1056-tiles-528x512", look_at((0.1, -3.0, 0.8), (0, 0, 0), 528, 512),
+                RasterParams(sh_degree=1), scb))
+    for name, n in (("small-path-2049-cam1", 2049), ("small-path-8192-cam1", 8192),
+                    ("general-path-8193-cam1", 8193)):
+        out.append((name, r.cams[1], r.params, {k: v[:n] for k, v in r.scene.items()}))
     return out
 
 
@@ -496,8 +502,25 @@ def test_split_backward(api, case, chunk, n_slots):
         assert np.array_equal(np32(fw["last"])[ok], np32(fw0["last"])[ok])
         assert (fw["out"] - fw0["out"]).abs().max().item() <= FWD_TOL
         assert (fw["final_T"] - fw0["final_T"]).abs().max().item() <= FWD_TOL
-    lens = np32(bins["tile_ranges"]).view(np.uint32).astype(np.int64)
-    print(f"  tiles longer than a chunk: {int(((lens[:, 1] - lens[:, 0]) > chunk).sum())}")
+    # a slot was taken for every chunk boundary that a walk crossed (64 chunks at
+    # most, the last open-ended) and for the end of each tile split, or asked for
+    # and not found
+    H16, W16 = -(-cam.height // 16) * 16, -(-cam.width // 16) * 16
+    last = np.zeros((H16, W16), np.int64)
+    last[:cam.height, :cam.width] = np32(fw["last"])
+    walk = last.reshape(H16 // 16, 16, W16 // 16, 16).max(axis=(1, 3))
+    crossed = np.minimum(np.maximum(walk - 1, 0) // chunk, 63)
+    taken = int(split["workspace"][:4].view(torch.int32))
+    print(f"  chunk boundaries crossed: {int(crossed.sum())}, slots asked for: {taken}")
+    whole = n_slots > crossed.sum() + (crossed > 0).sum()  # room for every tile
+    if whole:
+        assert taken >= crossed.sum() + (crossed > 0).sum()
+    else:
+        assert taken >= n_slots
+    if name == "deep-tile-48x48" and chunk == 256:
+        assert walk.max() > 64 * chunk  # the last chunk goes on past its own length
+    if name in ("deep-tile-48x48", "small-splats-100x75", "ring-all-cam5"):
+        assert crossed.sum() > 0
     for k in ("means", "log_scales", "quats", "opacity_logits", "sh"):
         a = np32(gs[k]).astype(np.float64)
         b = np32(g0[k]).astype(np.float64)
