@@ -1351,7 +1351,8 @@ __global__ __launch_bounds__(kSmallThreads) void bin_small_sort_kernel(
       s.val[0][i] = (uint16_t)i;
       s.rect[i] = pack_rect8(x0, y0, x1, y1);
       if (x1 >= x0) {
-        m += tt[it];
+        // the entries that are placed, whatever number tiles[] holds
+        m += (uint32_t)((x1 - x0 + 1) * (y1 - y0 + 1));
         atomicAdd(&diff[y0 * dw + x0], 1);
         atomicSub(&diff[y0 * dw + x1 + 1], 1);
         atomicSub(&diff[(y1 + 1) * dw + x0], 1);

@@ -458,3 +458,32 @@ def test_binning_collect_of_one_round(api, n, size):
     """Blocks of up to 2,048 Gaussians, whose rectangles the collection holds in
     registers: quarters of one to eight rounds of 64 positions, whole and not."""
     test_binning_small_block_sizes(api, n, size)
+
+
+@pytest.mark.parametrize("value", [1, 1 << 20])
+@pytest.mark.parametrize("n", [700, 2048, 2049, 8192, 8193])
+def test_binning_takes_tiles_touched_as_a_flag(api, n, value):
+    """A tiles_touched that only tells the Gaussians with a tile from those without:
+    the lists, and the count that the capacity is held against, are those of the
+    boxes, on every path; nothing is written past the capacity."""
+    from paper_2608_27735_amd.camera import RasterParams, look_at
+    r = S.rng(1500 + n)
+    cam = look_at((0.2, -3.0, 0.9), (0, 0, 0), 203, 117)
+    sc = S.gaussians(r, r.uniform(-1.5, 1.5, (n, 3)), 0, np.log(0.03), 0.6)
+    say("tiles as a flag", n, value)
+    proj = api.project(cam, RasterParams(sh_degree=0),
+                       **{k: torch.from_numpy(v).to(dev()) for k, v in sc.items()})
+    want = api.bin_sort(cam.width, cam.height, proj)
+    m = want["n_isect"]
+    assert m == int(proj["tiles_touched"].sum())
+    flag = dict(proj, tiles_touched=torch.where(proj["tiles_touched"] != 0, value, 0).to(torch.int32))
+    for capacity in (m, m - 1):
+        values = torch.full((m + 4096,), -7, dtype=torch.int32, device=dev())
+        got = api.bin_sort(cam.width, cam.height, flag, capacity=capacity, values=values, sync=False)
+        assert api.intersections(got["workspace"]) == m
+        if capacity == m:
+            assert torch.equal(got["tile_ranges"], want["tile_ranges"])
+            assert torch.equal(values[:m], want["values"][:m])
+            assert int((values[m:] != -7).sum()) == 0
+        else:
+            assert int(got["tile_ranges"].abs().max()) == 0 and int((values != -7).sum()) == 0
