@@ -11,8 +11,6 @@
 // alpha >= alpha_min ellipse reaches its pixels: the others cannot blend at any
 // of them, so the result is the same, and in tiles of many small
 // Gaussians a wave's walk is a fraction of the tile's list.
-#include <type_traits>
-
 #include "blend.h"
 
 namespace abcd {
@@ -322,16 +320,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
     rec = gather_rec(gid_next, nxt < end, means2d, conic_opacity, rgb);
     gid_next = gid_after;
     if (__ballot(amin_l < __builtin_huge_valf())) {
-      // The wave walks its own list kGroup entries at a time, 21 vector
-      // instructions per entry: a tile whose walk sets the launch's length has
-      // each SIMD of its CU to a single wave, which issues one instruction
-      // every 4.7 clocks (137 clocks per entry here), so the count is what it
-      // costs. The next group's geometry is read while this one blends and a
-      // group's colours while its alphas are computed, so no LDS latency is
+      // The wave walks its own list kGroup entries at a time, 85 vector
+      // instructions a group, 21 an entry: a tile whose walk sets the launch's
+      // length has each SIMD of its CU to a single wave, which issues one
+      // instruction every 4.7 clocks, some 100 clocks an entry, so the count is
+      // what it costs. The next group's geometry is read while this one blends
+      // and a group's colours while its alphas are computed, so no LDS latency is
       // waited for, and consecutive records make two entries one 16-byte read.
       // Against selects on the stop in every entry and reads through a list of
       // slots (28 instructions): 1M Gaussians at 1297x840 180 -> 151 us, 300K
-      // 167 -> 138, 4M tiny ones at 2560x1440 486 -> 390.
+      // 167 -> 138, 4M tiny ones at 2560x1440 486 -> 390, with the opacity inside
+      // the exponent; alpha as a product costs one instruction of that (on
+      // quadrants 145 -> 148, 129 -> 131 and 283 -> 288).
       int jl = -1;  // position in the wave's list of the last entry the lane blended
       float4 ga[kGroup];
       float2 gq[kGroup];
