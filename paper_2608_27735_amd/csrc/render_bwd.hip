@@ -148,6 +148,7 @@ struct BwdLds {
   float4 gc[256];     // colour b, list position, Gaussian
   float acc[9][257];  // [field][staged entry]; an entry's fields in different banks
   __align__(4) uint8_t idx[4][256];  // per wave: staged slots reaching its pixels
+  float4 box[4];  // per wave: box of its pixels whose walk reaches the batch
   int wcnt[5][4];
   uint32_t max;
 };
@@ -171,7 +172,6 @@ __device__ __forceinline__ void bwd_item(
   const int px = (tile % k.ntx) * kTile + quad_x(tid);
   const int py = (tile / k.ntx) * kTile + quad_y(tid);
   const bool inside = px < k.width && py < k.height;
-  const TileBox box = tile_box(k, tile);
   // Three rounds of loads before the walk: what the tile's arrays say (uniform),
   // the list's indices with the pixels' state, and the entries.
   const uint32_t start = tile_ranges[2 * tile];
@@ -252,12 +252,12 @@ __device__ __forceinline__ void bwd_item(
   float* const acc_lane = s.acc[adder ? field : 0];
   while (bend > bstop) {
     const uint32_t bbeg = bend - min(256u, bend - bstop);
+    const float4 box = live_box(k, tile, lastp > bbeg - start);
+    if ((tid & 63) == 0) s.box[tid >> 6] = box;
     __syncthreads();
-    const float3 cn = conic_of(rec.co);
-    // each wave walks only the staged entries whose ellipse reaches its
-    // quadrant: the others contribute nothing to any of its pixels
-    const uint32_t quads =
-        rec.valid ? splat_quads(rec.m.x, rec.m.y, cn.x, cn.y, cn.z, rec.co.w, k.alpha_min, box) : 0u;
+    // each wave walks only the staged entries whose ellipse reaches the box of
+    // its pixels whose walk reaches the batch: the others contribute nothing
+    const uint32_t quads = rec.valid ? splat_quads(rec.m, rec.co, k.alpha_min, s.box) : 0u;
     const bool keep = quads != 0u;
     int pos, wcnt;
     const int cnt = compact_rows(keep, quads, s.wcnt, s.idx, pos, wcnt);

@@ -26,6 +26,7 @@ struct FwdLds {
   float2 rg[4][kSlots];  // r, g
   float bl[4][kSlots];   // b
   uint8_t at[4][256];    // position in the batch
+  float4 box[4];         // per wave: box of its pixels that can still blend
   int wcnt[5][4];
   unsigned long long nb;
   uint32_t base;
@@ -239,7 +240,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
   const int px = (tile % k.ntx) * kTile + quad_x(tid);
   const int py = (tile / k.ntx) * kTile + quad_y(tid);
   const bool inside = px < k.width && py < k.height;
-  const TileBox box = tile_box(k, tile);
   const uint32_t start = tile_ranges[2 * tile], end = tile_ranges[2 * tile + 1];
   const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
   float T = 1.0f, cr = 0.0f, cg = 0.0f, cb = 0.0f;
@@ -285,6 +285,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
     rec = gather_rec(gid0, start + tid < end, means2d, conic_opacity, rgb);
   }
   for (uint32_t b0 = start; b0 < end; b0 += 256) {
+    const float4 box = live_box(k, tile, amin_l < __builtin_huge_valf());
+    if ((tid & 63) == 0) s.box[tid >> 6] = box;
     if (__syncthreads_count(amin_l == __builtin_huge_valf()) == 256) break;
     if (split_ok && b0 > start && (b0 - start) % chd == 0 && (b0 - start) / chd < kMaxChunks) {
       // state after the positions before b0; no pixel walks past a boundary
@@ -305,11 +307,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void r
         staged = 0;
       }
     }
-    const float3 cn = conic_of(rec.co);
-    // each wave walks only the staged entries whose ellipse reaches its
-    // quadrant: the others contribute nothing to any of its pixels
-    const uint32_t quads =
-        rec.valid ? splat_quads(rec.m.x, rec.m.y, cn.x, cn.y, cn.z, rec.co.w, k.alpha_min, box) : 0u;
+    // each wave walks only the staged entries whose ellipse reaches the box of
+    // its pixels that have not stopped: the others contribute nothing
+    const uint32_t quads = rec.valid ? splat_quads(rec.m, rec.co, k.alpha_min, s.box) : 0u;
     int wcnt;
     staged += (uint32_t)stage_fwd(s, rec, quads, wcnt);
     const int w = tid >> 6;

@@ -487,3 +487,49 @@ def test_binning_takes_tiles_touched_as_a_flag(api, n, value):
             assert int((values[m:] != -7).sum()) == 0
         else:
             assert int(got["tile_ranges"].abs().max()) == 0 and int((values != -7).sum()) == 0
+
+
+@pytest.mark.parametrize("size", [(151, 141), (275, 250), (530, 509)])
+def test_walks_past_the_pixels_that_have_stopped(api, size):
+    """An opaque cluster of small Gaussians before faint wide ones: the cluster's
+    pixels stop within the first batches, those at its rim and beyond walk on, so
+    each wave's box of pixels that still blend shrinks to a few columns and rows,
+    to nothing, or stays whole. Split (151x141), and unsplit with the backward that
+    takes tiles whole, directly and from the queue. Parity bars against the oracle."""
+    from paper_2608_27735_amd.camera import RasterParams, look_at
+    r = S.rng(1600)
+    cam = look_at((0.0, -3.0, 0.0), (0, 0, 0), *size)
+    prm = RasterParams(sh_degree=0)
+    near = S.gaussians(r, np.stack([0.12 * r.standard_normal(2600), r.uniform(-0.6, -0.2, 2600),
+                                    0.12 * r.standard_normal(2600)], 1), 0, np.log(0.012), 0.5)
+    near["opacity_logits"] += 1.5
+    far = S.gaussians(r, np.stack([r.uniform(-0.5, 0.5, 400), r.uniform(0.2, 0.6, 400),
+                                   r.uniform(-0.5, 0.5, 400)], 1), 0, np.log(0.06), 0.5)
+    far["opacity_logits"] -= 3.0
+    sc = {k: np.concatenate([near[k], far[k]]) for k in near}
+    F, B = S.background_pair(r, cam.height, cam.width)
+    say("stopped pixels", size)
+    ref = O.step(cam, prm, sc, F=F, B=B, rel_margin=1e-4)
+    knife = ref["fwd"]["knife"]
+    dL = np.where(knife[..., None], 0, S.upstream_grad(r, cam.height, cam.width)).astype(np.float32)
+    ref = O.step(cam, prm, sc, F=F, B=B, dL_dout=dL.astype(np.float64), rel_margin=1e-4)
+    last = ref["fwd"]["last"].astype(np.int64)
+    pad = np.zeros((-(-cam.height // 8) * 8, -(-cam.width // 8) * 8), np.int64)
+    pad[:cam.height, :cam.width] = last
+    quad = pad.reshape(pad.shape[0] // 8, 8, pad.shape[1] // 8, 8).transpose(0, 2, 1, 3).reshape(-1, 64)
+    # quadrants of which only some pixels walk past the end of a batch
+    some = np.stack([(quad > b).sum(1) for b in range(256, int(quad.max()), 256)])
+    assert ((some > 0) & (some < 32)).sum() >= 4 and (ref["fwd"]["final_T"][ref["fwd"]["last"] > 0] < 1e-3).any()
+    d = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to(dev())
+    params = {k: d(v) for k, v in sc.items()}
+    proj = api.project(cam, prm, **params)
+    bins = api.bin_sort(cam.width, cam.height, proj)
+    split = api.make_split(bins["n_isect"] // 256 + api.n_tiles(*size) + 1, 256) if size == (151, 141) else None
+    fwd = api.render_fwd(cam, prm, bins, proj, F=d(F), B=d(B), split=split)
+    grads = api.render_bwd(cam, prm, params, proj, bins, fwd, d(dL), F=d(F), B=d(B), split=split)
+    torch.cuda.synchronize()
+    assert np.abs(fwd["out"].cpu().numpy() - ref["fwd"]["out"])[~knife].max() <= 1e-5
+    assert np.array_equal(fwd["last"].cpu().numpy().view(np.uint32)[~knife], ref["fwd"]["last"][~knife])
+    for k in params:
+        g, gr = grads[k].cpu().numpy().astype(np.float64), ref["grads"][k]
+        assert np.linalg.norm(g - gr) <= 1e-4 * max(np.linalg.norm(gr), 1e-30), k
