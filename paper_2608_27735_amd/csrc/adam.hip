@@ -52,18 +52,18 @@ __device__ __forceinline__ void adam_one(float& th, float g, float& m, float& v,
 }
 
 // Up to kRows rows of kBlock vectors E (a float4 or a float) from the arrays'
-// start, n of them in all: thread t takes vector t of each row, so a wave's
-// accesses are consecutive, and every load is issued before the first is used
-// (an index past the end is clamped: a load under a condition would be waited
-// for where the branches meet).
-template <int kRows, typename E>
+// start, n of them in all (kFull: all of the rows'): thread t takes vector t of
+// each row, so a wave's accesses are consecutive, and every load is issued before
+// the first is used (an index past the end is clamped: a load under a condition
+// would be waited for where the branches meet).
+template <int kRows, typename E, bool kFull = false>
 __device__ __forceinline__ void adam_rows(float* th, const float* g, float* m, float* v, int n,
                                           float b1, float b2, float ic2, float eps, float step) {
   constexpr int kLanes = sizeof(E) / sizeof(float);
   E T[kRows], G[kRows], M[kRows], V[kRows];
 #pragma unroll
   for (int q = 0; q < kRows; ++q) {
-    const int i = min(q * kBlock + (int)threadIdx.x, n - 1);
+    const int t = q * kBlock + (int)threadIdx.x, i = kFull ? t : min(t, n - 1);
     T[q] = __builtin_nontemporal_load(reinterpret_cast<const E*>(th) + i);
     G[q] = __builtin_nontemporal_load(reinterpret_cast<const E*>(g) + i);
     M[q] = __builtin_nontemporal_load(reinterpret_cast<const E*>(m) + i);
@@ -78,7 +78,7 @@ __device__ __forceinline__ void adam_rows(float* th, const float* g, float* m, f
     float* const v1 = reinterpret_cast<float*>(&V[q]);
 #pragma unroll
     for (int e = 0; e < kLanes; ++e) adam_one(t1[e], g1[e], m1[e], v1[e], b1, b2, ic2, eps, step);
-    if (i < n) {
+    if (kFull || i < n) {
       __builtin_nontemporal_store(T[q], reinterpret_cast<E*>(th) + i);
       __builtin_nontemporal_store(M[q], reinterpret_cast<E*>(m) + i);
       __builtin_nontemporal_store(V[q], reinterpret_cast<E*>(v) + i);
@@ -101,7 +101,9 @@ __global__ __launch_bounds__(kBlock) void adam_kernel(AdamArgs a, float b1, floa
   if (a.vec[gi] && cnt >= 4) {
     // a group's last workgroup takes as many rows of float4 as it has
     const int n4 = cnt / 4;
-    if (n4 > 3 * kBlock)
+    if (n4 == 4 * kBlock)
+      adam_rows<4, f4v, true>(th, g, m, v, n4, b1, b2, ic2, eps, step);
+    else if (n4 > 3 * kBlock)
       adam_rows<4, f4v>(th, g, m, v, n4, b1, b2, ic2, eps, step);
     else if (n4 > 2 * kBlock)
       adam_rows<3, f4v>(th, g, m, v, n4, b1, b2, ic2, eps, step);
