@@ -248,14 +248,15 @@ constexpr int kRowsTiles = 256;
 // launched, and those that the tile's list has no use for return. With so few
 // pairs the whole chip would blend them in 10 us and the longest list sets the
 // launch's length. Each limit with both sides measured, in us, on 1,024 tiles:
-//   whole / rows: 1,024 Gaussians, longest list 718: 68 / 46; 16,000, longest
-//   1,862: 178 / 79;
-//   lists from 96 / 128 / 192 on in rows: 8,192 Gaussians over 769 tiles, longest
-//   list 185: 44 / 41 / 31 (whole 40), longest 611 over 206 tiles: 53 / 58 / 59;
-//   512 on 272 tiles, longest 222: 19 / 23 / 27 (whole 38). All lists in rows
-//   cost frames with many short ones: 1,024 over 675 tiles, longest 29, 15 -> 24.
-// The pairs' limit: 62,753 pairs over 61 tiles take 107 in rows, 274 whole; 84,814
-// over 917 tiles 63 in rows, 45 whole.
+//   whole / rows: 1,024 Gaussians, longest list 722: 65 / 42; 8,000 over 146 tiles,
+//   longest 1,263: 62 / 53; on 361 tiles 8,000, longest 2,707: 160 / 79;
+//   lists from 96 / 128 / 192 on in rows: 2,000 over 976 tiles, longest 186: 46 /
+//   42 / 35 (whole 35); 512 on 272 tiles, longest 222: 19 / 23 / 27 (whole 38),
+//   longest 444: 35 / 35 / 35 (whole 68). All lists in rows cost frames with many
+//   short ones: 1,024 over 675 tiles, longest 29, 15 -> 24.
+// The pairs' limit: 53,380 over 976 tiles are the worst below it (35 whole, 42
+// with rows); above, 77,052 pairs over 101 tiles would gain (113 / 86), 218,946
+// over 999 and 320,460 over 1,019 lose (55 / 76, 56 / 81).
 // The forward keeps one workgroup per tile in such frames: the rows layout
 // brought a few us where the lists are long (1,024 Gaussians over 149 of 1,024
 // tiles 31 -> 26) and cost 12 to 28 where they are spread out (over 864 of 1,024
